@@ -67,11 +67,10 @@ __device__ __forceinline__ R cdot(R ax, R ay, R az)
     return acc;
 }
 
-// c.q.c for a symmetric q given by its six components
+// c.q.c for a symmetric q given by its six components, added to acc
 template <int X, int Y, int Z, class R>
-__device__ __forceinline__ R cquad(R qxx, R qyy, R qzz, R qxy, R qxz, R qyz)
+__device__ __forceinline__ R cquad(R qxx, R qyy, R qzz, R qxy, R qxz, R qyz, R acc = R(-0.0))
 {
-    R acc = R(-0.0);
     if constexpr (X != 0) acc += R(X * X) * qxx;
     if constexpr (Y != 0) acc += R(Y * Y) * qyy;
     if constexpr (Z != 0) acc += R(Z * Z) * qzz;
@@ -135,52 +134,236 @@ __device__ __forceinline__ R ccc_dot(const Sym3<R>& t)
     return acc;
 }
 
-template <class L, int K, int KIND, bool PROJ, class R>
-__device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
+// The projection on the populations themselves: G' back onto sd = sum G and
+// j = sum c G.
+template <class L, class R>
+__device__ __forceinline__ void conserve(R (&G)[L::Q], R sd, R jx, R jy, R jz)
 {
-    static_assert(K >= 2 && K <= L::K_MAX, "Hermite order outside 2..2N-1");
-    static_assert(KIND == kFiltered || KIND == kBGK || (KIND == kFilteredQ && K >= 3), "collision kind");
+    constexpr int NP = (L::Q - 1) / 2;
+    constexpr R IT0 = R(L::INV_T0);
+    constexpr R IS = R(1.0 / L::S);
+    constexpr R NZ = R(-0.0);
+    R m0 = G[0], mx = NZ, my = NZ, mz = NZ;
+    unroll<NP>([&](auto P) {
+        constexpr int i = 2 * decltype(P)::value + 1;
+        constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+        const R dp = G[i] - G[i + 1];
+        m0 += G[i] + G[i + 1];
+        if constexpr (cx != 0) mx += R(cx) * dp;
+        if constexpr (cy != 0) my += R(cy) * dp;
+        if constexpr (cz != 0) mz += R(cz) * dp;
+    });
+    const R dm = (sd - m0) * IS;
+    const R dx = (jx - mx) * (IS * IT0);
+    const R dy = (jy - my) * (IS * IT0);
+    const R dz = (L::D == 3) ? (jz - mz) * (IS * IT0) : R(0);
+    G[0] += R(L::W[0]) * dm;
+    unroll<NP>([&](auto P) {
+        constexpr int i = 2 * decltype(P)::value + 1;
+        constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+        constexpr R Wi = R(L::W[i]);
+        const R cd = cdot<cx, cy, cz>(dx, dy, dz);
+        G[i] += Wi * (dm + cd);
+        G[i + 1] += Wi * (dm - cd);
+    });
+}
+
+// The same operator for K <= 3, regrouped by powers of c.  With n = om2 q and
+// t = rho u u, the even and odd parts of a pair are polynomials in c whose
+// coefficients are common to the site:
+//     Xe = E0 + c.M.c,           M = t / (2 T0^2) + n,
+//     Xo = c.l + a (c.N.c),      N = t / (6 T0^2) + n   (K = 3),
+//     E0 = (rho - 1) - tr t / (2 T0) - T0 tr n,   l = (1 + E0) u / T0 - 2 n.u,
+// (K = 2: Xo = rho a), and the rest particle has Xe = E0.  With n = 0 this is
+// the equilibrium that BGK relaxes to.  The energy flux adds Q.ccc - 3 T0 c.q
+// to Xo.
+// The conservation projection takes its sums from Xe and Xo (a pair's are 2 W Xe
+// and 2 W c Xo) and adds both corrections, dm +- c.dj / T0, to Xe before the
+// two populations are formed: Xe is the smaller of the two at low speed, so
+// the last sum is the only rounding that the projection leaves uncorrected, as
+// with a projection of the finished populations.  (BGK keeps that one: its old
+// populations enter last.)
+// Against the pair-by-pair form below this takes 290 instead of 377 executed
+// VALU instructions a D3Q19 FP32 site; measured where issue is the bound:
+// FP16 batch of 256 boxes 245 -> 227 us a step, 32^3 box 3.8 -> 3.65 us.  Its
+// FP32 error against an FP64 run is no larger (64^3 on a background flow, 1000
+// steps: 1.1e-6 against 2.0-2.8e-6 of the perturbation).
+template <class L, int K, int KIND, bool PROJ, class R>
+__device__ __forceinline__ void collide_low_order(R (&G)[L::Q], R omega, R theta, R sd, R drho, R inv_rho_s, R jx,
+                                                  R jy, R jz, R sxx, R syy, R szz, R sxy, R sxz, R syz)
+{
+    constexpr int NP = (L::Q - 1) / 2;
+    constexpr bool D3 = (L::D == 3);
+    constexpr bool BGK = (KIND == kBGK);
+    constexpr R IT0 = R(L::INV_T0);
+    constexpr R T0 = R(L::T0);
+    constexpr R IS = R(1.0 / L::S);
+    constexpr R NZ = R(-0.0);
+    constexpr R KM = R(0.5 * L::INV_T0 * L::INV_T0);
+    constexpr R KN = R(L::INV_T0 * L::INV_T0 / 6.0);
+
+    const R ux = jx * inv_rho_s, uy = jy * inv_rho_s, uz = D3 ? jz * inv_rho_s : R(0);
+    const R rx = jx * IS, ry = jy * IS, rz = D3 ? jz * IS : R(0);  // rho u
+    const R txx = rx * ux, tyy = ry * uy, txy = rx * uy;
+    R tzz = R(0), txz = R(0), tyz = R(0);
+    if constexpr (D3) {
+        tzz = rz * uz;
+        txz = rx * uz;
+        tyz = ry * uz;
+    }
+    const R trt = D3 ? txx + tyy + tzz : txx + tyy;
+
+    // n = om2 q, from Pi = sum c c G / S - (rho - 1) T0 I - t
+    R nxx = R(0), nyy = R(0), nzz = R(0), nxy = R(0), nxz = R(0), nyz = R(0);
+    R E0 = drho - R(0.5) * IT0 * trt;
+    if constexpr (!BGK) {
+        const R kn = omega * (R(0.5) * IT0 * IT0);
+        const R dT = drho * T0;
+        nxx = kn * (sxx * IS - dT - txx);
+        nyy = kn * (syy * IS - dT - tyy);
+        nxy = kn * (sxy * IS - txy);
+        if constexpr (D3) {
+            nzz = kn * (szz * IS - dT - tzz);
+            nxz = kn * (sxz * IS - txz);
+            nyz = kn * (syz * IS - tyz);
+        }
+        E0 -= T0 * (D3 ? nxx + nyy + nzz : nxx + nyy);
+    }
+    const R mxx = fused(KM, txx, nxx), myy = fused(KM, tyy, nyy), mxy = fused(KM, txy, nxy);
+    const R mzz = fused(KM, tzz, nzz), mxz = fused(KM, txz, nxz), myz = fused(KM, tyz, nyz);
+    const R uqx = ux * IT0, uqy = uy * IT0, uqz = uz * IT0;
+    R lx, ly, lz = R(0);
+    R Nxx = R(0), Nyy = R(0), Nzz = R(0), Nxy = R(0), Nxz = R(0), Nyz = R(0);
+    if constexpr (K == 2) {
+        lx = IT0 * rx;  // rho a
+        ly = IT0 * ry;
+        if constexpr (D3) lz = IT0 * rz;
+    } else {
+        const R g = R(1) + E0;
+        if constexpr (BGK) {
+            lx = g * uqx;
+            ly = g * uqy;
+            if constexpr (D3) lz = g * uqz;
+        } else {
+            R bx = nxx * ux + nxy * uy, by = nxy * ux + nyy * uy;
+            if constexpr (D3) {
+                bx += nxz * uz;
+                by += nyz * uz;
+                lz = g * uqz - R(2) * (nxz * ux + nyz * uy + nzz * uz);
+            }
+            lx = g * uqx - R(2) * bx;
+            ly = g * uqy - R(2) * by;
+        }
+        Nxx = fused(KN, txx, nxx);
+        Nyy = fused(KN, tyy, nyy);
+        Nxy = fused(KN, txy, nxy);
+        if constexpr (D3) {
+            Nzz = fused(KN, tzz, nzz);
+            Nxz = fused(KN, txz, nxz);
+            Nyz = fused(KN, tyz, nyz);
+        }
+    }
+
+    // Energy flux: Qt scaled by omega theta / (6 T0^3), the factor of fhat^q
+    // in stored units.
+    Sym3<R> Qs{};
+    if constexpr (KIND == kFilteredQ) {
+        // S sum c c c (G - G^eq): only the odd part G_+ - G_- of each pair
+        // counts; rho Po_3 = a (rho - rho v / 2 + (c.t.c) / (6 T0^2))
+        Sym3<R> t{NZ, NZ, NZ, NZ, NZ, NZ, NZ, NZ, NZ, NZ};
+        const R ge = (R(1) + drho) - R(0.5) * IT0 * trt;
+        const R exx = KN * txx, eyy = KN * tyy, ezz = KN * tzz, exy = KN * txy, exz = KN * txz, eyz = KN * tyz;
+        unroll<NP>([&](auto P) {
+            constexpr int i = 2 * decltype(P)::value + 1;
+            constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+            const R po = cdot<cx, cy, cz>(uqx, uqy, uqz) * (ge + cquad<cx, cy, cz>(exx, eyy, ezz, exy, exz, eyz));
+            const R dneq = (G[i] - G[i + 1]) - R(2 * L::W[i]) * po;
+            add_ccc<cx, cy, cz>(t, dneq);
+        });
+        const R cs = omega * theta * R(1.0 / (6.0 * L::T0 * L::T0 * L::T0)) * IS;
+        const R cp = theta * R(1.0 / (3.0 * L::T0));  // takes n to omega theta Pi / (6 T0^3)
+        const R ax = cp * ux, ay = cp * uy, az = cp * uz;
+        Qs.xxx = t.xxx * cs - R(3) * ax * nxx;
+        Qs.xxy = t.xxy * cs - (R(2) * ax * nxy + ay * nxx);
+        Qs.xyy = t.xyy * cs - (R(2) * ay * nxy + ax * nyy);
+        Qs.yyy = t.yyy * cs - R(3) * ay * nyy;
+        if constexpr (D3) {
+            Qs.xxz = t.xxz * cs - (R(2) * ax * nxz + az * nxx);
+            Qs.xyz = t.xyz * cs - (ax * nyz + ay * nxz + az * nxy);
+            Qs.xzz = t.xzz * cs - (R(2) * az * nxz + ax * nzz);
+            Qs.yyz = t.yyz * cs - (R(2) * ay * nyz + az * nyy);
+            Qs.yzz = t.yzz * cs - (R(2) * az * nyz + ay * nzz);
+            Qs.zzz = t.zzz * cs - R(3) * az * nzz;
+        }
+        lx -= R(3) * T0 * (Qs.xxx + Qs.xyy + Qs.xzz);
+        ly -= R(3) * T0 * (Qs.xxy + Qs.yyy + Qs.yzz);
+        if constexpr (D3) lz -= R(3) * T0 * (Qs.xxz + Qs.yyz + Qs.zzz);
+    }
+
+    R Xe[NP], Xo[NP];
+    unroll<NP>([&](auto P) {
+        constexpr int p = decltype(P)::value, i = 2 * p + 1;
+        constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+        Xe[p] = cquad<cx, cy, cz>(mxx, myy, mzz, mxy, mxz, myz, E0);
+        Xo[p] = cdot<cx, cy, cz>(lx, ly, lz);
+        if constexpr (K == 3)
+            Xo[p] = fused(cdot<cx, cy, cz>(uqx, uqy, uqz), cquad<cx, cy, cz>(Nxx, Nyy, Nzz, Nxy, Nxz, Nyz), Xo[p]);
+        if constexpr (KIND == kFilteredQ) Xo[p] += ccc_dot<cx, cy, cz>(Qs);
+    });
+
+    if constexpr (PROJ && !BGK) {
+        R m0 = R(L::W[0]) * E0, mx = NZ, my = NZ, mz = NZ;
+        unroll<NP>([&](auto P) {
+            constexpr int p = decltype(P)::value, i = 2 * p + 1;
+            constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+            constexpr int W2 = 2 * L::W[i];
+            m0 = fused(R(W2), Xe[p], m0);
+            if constexpr (cx != 0) mx = fused(R(W2 * cx), Xo[p], mx);
+            if constexpr (cy != 0) my = fused(R(W2 * cy), Xo[p], my);
+            if constexpr (cz != 0) mz = fused(R(W2 * cz), Xo[p], mz);
+        });
+        const R dm = (sd - m0) * IS;
+        const R dx = (jx - mx) * (IS * IT0);
+        const R dy = (jy - my) * (IS * IT0);
+        const R dz = D3 ? (jz - mz) * (IS * IT0) : R(0);
+        G[0] = R(L::W[0]) * (E0 + dm);
+        unroll<NP>([&](auto P) {
+            constexpr int p = decltype(P)::value, i = 2 * p + 1;
+            constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+            constexpr R Wi = R(L::W[i]);
+            const R cd = cdot<cx, cy, cz>(dx, dy, dz);
+            const R e = Xe[p] + dm, WXo = Wi * Xo[p];
+            G[i] = fused(Wi, e + cd, WXo);
+            G[i + 1] = fused(Wi, e - cd, -WXo);
+        });
+    } else {
+        const R g0 = R(L::W[0]) * E0;
+        G[0] = BGK ? g0 + omega * (G[0] - g0) : g0;
+        unroll<NP>([&](auto P) {
+            constexpr int p = decltype(P)::value, i = 2 * p + 1;
+            constexpr R Wi = R(L::W[i]);
+            const R WXo = Wi * Xo[p];
+            const R gp = fused(Wi, Xe[p], WXo), gm = fused(Wi, Xe[p], -WXo);
+            G[i] = BGK ? gp + omega * (G[i] - gp) : gp;
+            G[i + 1] = BGK ? gm + omega * (G[i + 1] - gm) : gm;
+        });
+        if constexpr (PROJ) conserve<L, R>(G, sd, jx, jy, jz);
+    }
+}
+
+// The operator for K >= 4 (D3Q39), pair by pair.
+template <class L, int K, int KIND, bool PROJ, class R>
+__device__ __forceinline__ void collide_high_order(R (&G)[L::Q], R omega, R theta, R sd, R drho, R inv_rho_s, R jx,
+                                                   R jy, R jz, R sxx, R syy, R szz, R sxy, R sxz, R syz)
+{
+    static_assert(K >= 4, "lower orders: collide_low_order");
     constexpr int NP = (L::Q - 1) / 2;  // opposite pairs (2p+1, 2p+2)
     constexpr bool D3 = (L::D == 3);
     constexpr R IT0 = R(L::INV_T0);
     constexpr R T0 = R(L::T0);
-    constexpr R SR = R(L::S);
     constexpr R IS = R(1.0 / L::S);
     constexpr R NZ = R(-0.0);
 
-    // zeroth, first and second moments (eq. mme, eq. Mflux), scaled by S,
-    // from pair sums s = G_+ + G_- and differences d = G_+ - G_-
-    R sd = G[0], jx = NZ, jy = NZ, jz = NZ;
-    R sxx = NZ, syy = NZ, szz = NZ, sxy = NZ, sxz = NZ, syz = NZ;
-    unroll<NP>([&](auto P) {
-        constexpr int i = 2 * decltype(P)::value + 1;
-        constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-        const R sp = G[i] + G[i + 1];
-        const R dp = G[i] - G[i + 1];
-        sd += sp;
-        if constexpr (cx != 0) jx += R(cx) * dp;
-        if constexpr (cy != 0) jy += R(cy) * dp;
-        if constexpr (cz != 0) jz += R(cz) * dp;
-        if constexpr (cx != 0) sxx += R(cx * cx) * sp;
-        if constexpr (cy != 0) syy += R(cy * cy) * sp;
-        if constexpr (cz != 0) szz += R(cz * cz) * sp;
-        if constexpr (cx * cy != 0) sxy += R(cx * cy) * sp;
-        if constexpr (cx * cz != 0) sxz += R(cx * cz) * sp;
-        if constexpr (cy * cz != 0) syz += R(cy * cz) * sp;
-    });
-
-    // In single precision 1 / (S rho) is the hardware reciprocal (about one
-    // unit in the last place) and sd / S a product with the rounded 1 / S:
-    // an IEEE division is some ten instructions, and these single-precision
-    // steps are bound by instruction issue at 16-bit storage.
-    R drho, inv_rho_s;  // rho - 1 and 1 / (S rho)
-    if constexpr (std::is_same<R, float>::value) {
-        drho = sd * IS;
-        inv_rho_s = __builtin_amdgcn_rcpf(SR + sd);
-    } else {
-        drho = sd / SR;
-        inv_rho_s = R(1) / (SR + sd);
-    }
     const R rho = R(1) + drho;
     const R ux = jx * inv_rho_s, uy = jy * inv_rho_s;
     const R uz = D3 ? jz * inv_rho_s : R(0);
@@ -225,19 +408,13 @@ __device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
     auto eq_parts = [&](R a, R& Ee, R& Po) {
         const R h2 = a * a - v;
         Ee = R(0.5) * h2;
-        if constexpr (K == 2) {
-            Po = a;
-        } else {
-            const R h3 = a * (h2 - R(2) * v);
-            Po = a + R(1.0 / 6.0) * h3;
-            if constexpr (K >= 4) {
-                const R h4 = a * h3 - R(3) * v * h2;
-                Ee = Ee + R(1.0 / 24.0) * h4;
-                if constexpr (K == 5) {
-                    const R h5 = a * h4 - R(4) * v * h3;
-                    Po = Po + R(1.0 / 120.0) * h5;
-                }
-            }
+        const R h3 = a * (h2 - R(2) * v);
+        Po = a + R(1.0 / 6.0) * h3;
+        const R h4 = a * h3 - R(3) * v * h2;
+        Ee = Ee + R(1.0 / 24.0) * h4;
+        if constexpr (K == 5) {
+            const R h5 = a * h4 - R(4) * v * h3;
+            Po = Po + R(1.0 / 120.0) * h5;
         }
     };
 
@@ -278,15 +455,13 @@ __device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
         qsx = Qs.xxx + Qs.xyy + Qs.xzz;
         qsy = Qs.xxy + Qs.yyy + Qs.yzz;
         qsz = Qs.xxz + Qs.yyz + Qs.zzz;
-        if constexpr (K >= 4) {
-            rxx = Qs.xxx * ux + Qs.xxy * uy + Qs.xxz * uz;
-            ryy = Qs.xyy * ux + Qs.yyy * uy + Qs.yyz * uz;
-            rzz = Qs.xzz * ux + Qs.yzz * uy + Qs.zzz * uz;
-            rxy = Qs.xxy * ux + Qs.xyy * uy + Qs.xyz * uz;
-            rxz = Qs.xxz * ux + Qs.xyz * uy + Qs.xzz * uz;
-            ryz = Qs.xyz * ux + Qs.yyz * uy + Qs.yzz * uz;
-            d1u = R(3) * T0 * (qsx * ux + qsy * uy + qsz * uz);
-        }
+        rxx = Qs.xxx * ux + Qs.xxy * uy + Qs.xxz * uz;
+        ryy = Qs.xyy * ux + Qs.yyy * uy + Qs.yyz * uz;
+        rzz = Qs.xzz * ux + Qs.yzz * uy + Qs.zzz * uz;
+        rxy = Qs.xxy * ux + Qs.xyy * uy + Qs.xyz * uz;
+        rxz = Qs.xxz * ux + Qs.xyz * uy + Qs.xzz * uz;
+        ryz = Qs.xyz * ux + Qs.yyz * uy + Qs.yzz * uz;
+        d1u = R(3) * T0 * (qsx * ux + qsy * uy + qsz * uz);
         if constexpr (K >= 5) {
             rsx = rxx * ux + rxy * uy + rxz * uz;
             rsy = rxy * ux + ryy * uy + ryz * uz;
@@ -303,19 +478,14 @@ __device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
         // rest particle: a = 0, B = 0, A = -tr Pi, h2 = -v, h3 = 0, h4 = 3 v^2
         const R A0 = -trP;
         const R Ee2 = R(-0.5) * v;
-        R Ee = Ee2;
-        if constexpr (K >= 4) Ee = Ee2 + R(0.125) * v * v;
+        const R Ee = Ee2 + R(0.125) * v * v;
         R Xe;
         if constexpr (KIND == kBGK) {
             const R geq = R(L::W[0]) * (drho + rho * Ee);
             Xe = geq + omega * (G[0] - geq);
         } else {
-            if constexpr (K <= 3) {
-                Xe = drho + rho * Ee + om2 * A0;
-            } else {
-                Xe = drho + rho * Ee + om2 * (A0 + A0 * Ee2 + Cs);
-            }
-            if constexpr (KIND == kFilteredQ && K >= 4) Xe += d1u;
+            Xe = drho + rho * Ee + om2 * (A0 + A0 * Ee2 + Cs);
+            if constexpr (KIND == kFilteredQ) Xe += d1u;
             Xe = R(L::W[0]) * Xe;
         }
         G[0] = Xe;
@@ -338,45 +508,31 @@ __device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
             const R A = cquad<cx, cy, cz>(qxx, qyy, qzz, qxy, qxz, qyz) - trP;
             const R h2 = a * a - v;
             const R Ee2 = R(0.5) * h2;
-            R Xe, Xo;
-            if constexpr (K == 2) {
-                Xe = drho + rho * Ee2 + om2 * A;
-                Xo = rho * a;
+            const R B = cdot<cx, cy, cz>(bqx, bqy, bqz);
+            const R h3 = a * (h2 - R(2) * v);
+            const R Po3 = a + R(1.0 / 6.0) * h3;
+            const R h4 = a * h3 - R(3) * v * h2;
+            const R Ee4 = Ee2 + R(1.0 / 24.0) * h4;
+            const R Ne = A + A * Ee2 - B * a + Cs;
+            R Xe = drho + rho * Ee4 + om2 * Ne;
+            R Xo;
+            if constexpr (K == 4) {
+                Xo = rho * Po3 + om2 * (A * a - B);
             } else {
-                const R B = cdot<cx, cy, cz>(bqx, bqy, bqz);
-                const R h3 = a * (h2 - R(2) * v);
-                const R Po3 = a + R(1.0 / 6.0) * h3;
-                if constexpr (K == 3) {
-                    Xe = drho + rho * Ee2 + om2 * A;
-                    Xo = rho * Po3 + om2 * (A * a - B);
+                const R h5 = a * h4 - R(4) * v * h3;
+                const R Po5 = Po3 + R(1.0 / 120.0) * h5;
+                Xo = rho * Po5 + om2 * (A * Po3 - B - B * Ee2 + Cs * a);
+            }
+            if constexpr (KIND == kFilteredQ) {
+                // d0 (odd), d1 (even), d2 (odd) of the energy-flux part
+                const R d0 = ccc_dot<cx, cy, cz>(Qs) - R(3) * T0 * cdot<cx, cy, cz>(qsx, qsy, qsz);
+                const R d1 = d1u - R(3) * cquad<cx, cy, cz>(rxx, ryy, rzz, rxy, rxz, ryz);
+                Xe += d0 * a + d1;
+                if constexpr (K == 4) {
+                    Xo += d0;
                 } else {
-                    const R h4 = a * h3 - R(3) * v * h2;
-                    const R Ee4 = Ee2 + R(1.0 / 24.0) * h4;
-                    const R Ne = A + A * Ee2 - B * a + Cs;
-                    Xe = drho + rho * Ee4 + om2 * Ne;
-                    if constexpr (K == 4) {
-                        Xo = rho * Po3 + om2 * (A * a - B);
-                    } else {
-                        const R h5 = a * h4 - R(4) * v * h3;
-                        const R Po5 = Po3 + R(1.0 / 120.0) * h5;
-                        Xo = rho * Po5 + om2 * (A * Po3 - B - B * Ee2 + Cs * a);
-                    }
-                }
-                if constexpr (KIND == kFilteredQ) {
-                    // d0 (odd), d1 (even), d2 (odd) of the energy-flux part
-                    const R d0 = ccc_dot<cx, cy, cz>(Qs) - R(3) * T0 * cdot<cx, cy, cz>(qsx, qsy, qsz);
-                    if constexpr (K == 3) {
-                        Xo += d0;
-                    } else {
-                        const R d1 = d1u - R(3) * cquad<cx, cy, cz>(rxx, ryy, rzz, rxy, rxz, ryz);
-                        Xe += d0 * a + d1;
-                        if constexpr (K == 4) {
-                            Xo += d0;
-                        } else {
-                            const R d2 = R(3) * cdot<cx, cy, cz>(rsx, rsy, rsz);
-                            Xo += d0 * (R(1) + Ee2) + d1 * a + d2;
-                        }
-                    }
+                    const R d2 = R(3) * cdot<cx, cy, cz>(rsx, rsy, rsz);
+                    Xo += d0 * (R(1) + Ee2) + d1 * a + d2;
                 }
             }
             // W (Xe +- Xo) as W Xe +- W Xo: one product and two fused
@@ -387,31 +543,58 @@ __device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
         }
     });
 
-    if constexpr (PROJ) {
-        R m0 = G[0], mx = NZ, my = NZ, mz = NZ;
-        unroll<NP>([&](auto P) {
-            constexpr int i = 2 * decltype(P)::value + 1;
-            constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-            const R dp = G[i] - G[i + 1];
-            m0 += G[i] + G[i + 1];
-            if constexpr (cx != 0) mx += R(cx) * dp;
-            if constexpr (cy != 0) my += R(cy) * dp;
-            if constexpr (cz != 0) mz += R(cz) * dp;
-        });
-        const R dm = (sd - m0) * IS;
-        const R dx = (jx - mx) * (IS * IT0);
-        const R dy = (jy - my) * (IS * IT0);
-        const R dz = D3 ? (jz - mz) * (IS * IT0) : R(0);
-        G[0] += R(L::W[0]) * dm;
-        unroll<NP>([&](auto P) {
-            constexpr int i = 2 * decltype(P)::value + 1;
-            constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-            constexpr R Wi = R(L::W[i]);
-            const R cd = cdot<cx, cy, cz>(dx, dy, dz);
-            G[i] += Wi * (dm + cd);
-            G[i + 1] += Wi * (dm - cd);
-        });
+    if constexpr (PROJ) conserve<L, R>(G, sd, jx, jy, jz);
+}
+
+template <class L, int K, int KIND, bool PROJ, class R>
+__device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
+{
+    static_assert(K >= 2 && K <= L::K_MAX, "Hermite order outside 2..2N-1");
+    static_assert(KIND == kFiltered || KIND == kBGK || (KIND == kFilteredQ && K >= 3), "collision kind");
+    constexpr int NP = (L::Q - 1) / 2;  // opposite pairs (2p+1, 2p+2)
+    constexpr R SR = R(L::S);
+    constexpr R IS = R(1.0 / L::S);
+    constexpr R NZ = R(-0.0);
+
+    // zeroth, first and second moments (eq. mme, eq. Mflux), scaled by S,
+    // from pair sums s = G_+ + G_- and differences d = G_+ - G_-
+    R sd = G[0], jx = NZ, jy = NZ, jz = NZ;
+    R sxx = NZ, syy = NZ, szz = NZ, sxy = NZ, sxz = NZ, syz = NZ;
+    unroll<NP>([&](auto P) {
+        constexpr int i = 2 * decltype(P)::value + 1;
+        constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+        const R sp = G[i] + G[i + 1];
+        const R dp = G[i] - G[i + 1];
+        sd += sp;
+        if constexpr (cx != 0) jx += R(cx) * dp;
+        if constexpr (cy != 0) jy += R(cy) * dp;
+        if constexpr (cz != 0) jz += R(cz) * dp;
+        if constexpr (cx != 0) sxx += R(cx * cx) * sp;
+        if constexpr (cy != 0) syy += R(cy * cy) * sp;
+        if constexpr (cz != 0) szz += R(cz * cz) * sp;
+        if constexpr (cx * cy != 0) sxy += R(cx * cy) * sp;
+        if constexpr (cx * cz != 0) sxz += R(cx * cz) * sp;
+        if constexpr (cy * cz != 0) syz += R(cy * cz) * sp;
+    });
+
+    // In single precision 1 / (S rho) is the hardware reciprocal (about one
+    // unit in the last place) and sd / S a product with the rounded 1 / S:
+    // an IEEE division is some ten instructions, and these single-precision
+    // steps are bound by instruction issue at 16-bit storage.
+    R drho, inv_rho_s;  // rho - 1 and 1 / (S rho)
+    if constexpr (std::is_same<R, float>::value) {
+        drho = sd * IS;
+        inv_rho_s = __builtin_amdgcn_rcpf(SR + sd);
+    } else {
+        drho = sd / SR;
+        inv_rho_s = R(1) / (SR + sd);
     }
+    if constexpr (K <= 3)
+        collide_low_order<L, K, KIND, PROJ, R>(G, omega, theta, sd, drho, inv_rho_s, jx, jy, jz, sxx, syy, szz, sxy,
+                                               sxz, syz);
+    else
+        collide_high_order<L, K, KIND, PROJ, R>(G, omega, theta, sd, drho, inv_rho_s, jx, jy, jz, sxx, syy, szz, sxy,
+                                                sxz, syz);
 }
 
 // Equilibrium in stored units, G_i = S (f^eq_i - w_i) (eq. hermite truncated at K).
