@@ -53,7 +53,13 @@ lbm_status fail_hip(hipError_t e, const char* what)
         if (e_ != hipSuccess) return fail_hip(e_, what); \
     } while (0)
 
-constexpr int kChunkSites = 4096;   // sites per reduction chunk
+constexpr int kChunkSites = 4096;   // most sites of a reduction chunk
+constexpr int kMinChunkSites = 256; // fewest, but for a box's last chunk
+// Small boxes take smaller chunks, down to one site per thread: a 16^3 box as
+// one chunk left a single block with sixteen loads in series (k_moments 19 us,
+// k_init 25 us).  2048 chunks are eight blocks per compute unit, where the
+// kernels are bound by HBM and larger chunks keep the final reduction short.
+constexpr int kManyChunks = 2048;
 constexpr int kDefaultGraphChunk = 32;
 constexpr int kTuneRounds = 3;
 
@@ -110,6 +116,7 @@ struct lbm_ctx {
     // reductions
     ChunkDesc* d_chunks = nullptr;
     int nchunks = 0;
+    int chunk_sites = kChunkSites;
     int* d_box_chunk_begin = nullptr;
     double* d_partial = nullptr;
     double* d_out = nullptr;
@@ -319,14 +326,32 @@ lbm_status create_common(lbm_t* out, int32_t lattice, int32_t nbox, const int64_
         if (e != hipSuccess) return cleanup(fail_hip(e, "hipStreamCreate"));
 
         // reduction chunks (never straddle two boxes)
+        int chunk = kMinChunkSites;
+        for (; chunk < kChunkSites; chunk *= 2) {
+            int64_t n = 0;
+            for (int b = 0; b < nbox; ++b)
+                n += (dims[3 * b] * dims[3 * b + 1] * dims[3 * b + 2] + chunk - 1) / chunk;
+            if (n <= kManyChunks) break;
+        }
+        h->chunk_sites = chunk;
         std::vector<ChunkDesc> chunks;
         std::vector<int> begin;
         for (int b = 0; b < nbox; ++b) {
             begin.push_back(int(chunks.size()));
             const int64_t n = dims[3 * b] * dims[3 * b + 1] * dims[3 * b + 2];
-            for (int64_t s = 0; s < n; s += kChunkSites) {
-                const int64_t cnt = (n - s < kChunkSites) ? (n - s) : kChunkSites;
-                chunks.push_back({h->offset[b] + s, int(cnt), b});
+            const int64_t w = (nbox == 1) ? dims[3 * b] : kBlockSites;
+            for (int64_t s = 0; s < n; s += chunk) {
+                ChunkDesc c{};
+                c.start = h->offset[b] + s;
+                c.row0 = s / w;
+                c.count = int(std::min<int64_t>(chunk, n - s));
+                c.box = b;
+                c.x0 = int(s % w);
+                if (nbox == 1) {
+                    c.y0 = int(c.row0 % dims[1]);
+                    c.z0 = int(c.row0 / dims[1]);
+                }
+                chunks.push_back(c);
             }
         }
         begin.push_back(int(chunks.size()));
@@ -820,8 +845,7 @@ lbm_status lbm_init(lbm_t h, const double* rho, const double* u, int32_t on_devi
             return st;
         }
         hipError_t e = launch_init(h->lattice, h->dtype, h->K, twisted(h) ? kTwistEven : kNatural, drho, du, h->buf[0],
-                                   h->d_chunks, h->nchunks, h->d_boxes,
-                                   h->nsites, h->stream);
+                                   h->d_chunks, h->nchunks, h->chunk_sites, h->d_boxes, h->nsites, h->stream);
         hipError_t e2 = hipStreamSynchronize(h->stream);
         if (t1) (void)hipFree(drho);
         if (t2) (void)hipFree(du);
@@ -1063,7 +1087,7 @@ lbm_status lbm_moments(lbm_t h, double* rho, double* u, int32_t on_device)
         int layout = kNatural;
         state_view(h, &state, &layout);
         hipError_t e = launch_moments(h->lattice, h->dtype, state, layout, drho, du, h->d_chunks, h->nchunks,
-                                      h->d_boxes, h->nsites, h->stream);
+                                      h->chunk_sites, h->d_boxes, h->nsites, h->stream);
         if (e == hipSuccess && !on_device) {
             e = hipMemcpyAsync(rho, drho, n * sizeof(double), hipMemcpyDeviceToHost, h->stream);
             if (e == hipSuccess) e = hipMemcpyAsync(u, du, n * D * sizeof(double), hipMemcpyDeviceToHost, h->stream);

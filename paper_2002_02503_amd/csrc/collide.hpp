@@ -54,6 +54,21 @@ __device__ __forceinline__ R fused(R a, R b, R c)
     else return __builtin_fma(a, b, c);
 }
 
+// x / N in double, rounded as the division is, for a small integer N: with the
+// correctly rounded 1 / N the quotient is off by at most one unit in the last
+// place and its exact remainder corrects it (Markstein).  An infinite x leaves
+// no remainder and keeps the quotient.  An FP64 division is some 25
+// instructions.
+template <int N>
+__device__ __forceinline__ double over(double x)
+{
+    constexpr double inv = 1.0 / N;
+    const double q = x * inv;
+    if constexpr ((N & (N - 1)) == 0) return q;
+    const double r = __builtin_fma(-double(N), q, x);
+    return r == r ? __builtin_fma(r, inv, q) : q;
+}
+
 // Sparse dot products with compile-time integer coefficients: zero terms are
 // dropped and the sum starts from -0.0, which IEEE addition leaves unchanged,
 // so no "0 + x" or "0 * x" survives into the instruction stream.
@@ -598,9 +613,10 @@ __device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
 }
 
 // Equilibrium in stored units, G_i = S (f^eq_i - w_i) (eq. hermite truncated at K).
-template <class L, int K, class R>
-__device__ __forceinline__ void equilibrium_scaled(R drho, R ux, R uy, R uz, R (&G)[L::Q])
+template <class L, int K>
+__device__ __forceinline__ void equilibrium_scaled(double drho, double ux, double uy, double uz, double (&G)[L::Q])
 {
+    using R = double;
     constexpr R IT0 = R(L::INV_T0);
     const R v = (ux * ux + uy * uy + uz * uz) * IT0;
     unroll<L::Q>([&](auto I) {
@@ -609,14 +625,14 @@ __device__ __forceinline__ void equilibrium_scaled(R drho, R ux, R uy, R uz, R (
         constexpr R Wi = R(L::W[i]);
         const R a = (R(cx) * ux + R(cy) * uy + R(cz) * uz) * IT0;
         R hm1 = R(1), h = a, E = a;
-        R fact = R(1);
-        for (int n = 1; n < K; ++n) {
+        unroll<K - 1>([&](auto N) {
+            constexpr int n = decltype(N)::value + 1;
+            constexpr int fact[] = {1, 1, 2, 6, 24, 120};
             const R hn = a * h - R(n) * v * hm1;
             hm1 = h;
             h = hn;
-            fact *= R(n + 1);
-            E += h / fact;
-        }
+            E += over<fact[n + 1]>(h);
+        });
         G[i] = Wi * (drho * (R(1) + E) + E);
     });
 }

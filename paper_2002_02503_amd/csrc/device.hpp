@@ -98,16 +98,16 @@ __device__ __forceinline__ T* at32(T* p, unsigned i)
     return reinterpret_cast<T*>(reinterpret_cast<B*>(p) + unsigned(i * unsigned(sizeof(T))));
 }
 
-// Periodic wrap of a coordinate v in [-3, n + 2] onto [0, n).
+// Periodic wrap of a coordinate v in [-3, n + 2] onto [0, n).  One period off
+// at most from n = 3 on; for n = 1 and 2 the mask n - 1 does it (a remainder
+// in their place put some 25 instructions for each wrapped coordinate into
+// every kernel).
 __device__ __forceinline__ int wrap_coord(int v, int n)
 {
-    if (n >= 3) {
-        v += (v < 0) ? n : 0;
-        v -= (v >= n) ? n : 0;
-        return v;
-    }
-    v %= n;
-    return v < 0 ? v + n : v;
+    v &= (n < 3) ? n - 1 : -1;
+    v += (v < 0) ? n : 0;
+    v -= (v >= n) ? n : 0;
+    return v;
 }
 
 // A population the step pulls.  Rows read at their own x (c_x = 0) are read

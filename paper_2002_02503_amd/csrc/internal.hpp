@@ -81,18 +81,23 @@ struct BoxDesc {
 };
 
 // A run of `count` consecutive global sites of one box (never two boxes),
-// the unit of the set-up, moment and reduction kernels.
+// the unit of the set-up, moment and reduction kernels, with the place of its
+// first site: block row0 of the box's layout, position x0 in it (for a single
+// box the x-row and x) and, for a single box, that row's y0 and z0.
 struct ChunkDesc {
     long long start;
+    long long row0;
     int count;
     int box;
+    int x0, y0, z0;
 };
 
 // Kernel launchers (kernels.hip).  All return hipSuccess or the first error.
+// chunk_sites: the largest chunk's sites.
 // layout: kNatural, or kTwistEven for a single box stepped by k_step_tw.
 hipError_t launch_init(int lat, int dtype, int K, int layout, const double* rho, const double* u, void* dst,
-                       const ChunkDesc* chunks, int nchunks, const BoxDesc* boxes, long long nsites,
-                       hipStream_t s);
+                       const ChunkDesc* chunks, int nchunks, int chunk_sites, const BoxDesc* boxes,
+                       long long nsites, hipStream_t s);
 // The fused step.  kind: collision kind (collide.hpp: 0 filtered, 1 BGK,
 // 2 filtered with the energy-flux term of weight theta).
 // pair: two sites per thread (rows 2j, 2j + 1; ny even).
@@ -126,7 +131,8 @@ hipError_t launch_step_batch(int lat, int dtype, int K, int kind, const void* sr
 // Readers of the stored state, in any StateLayout (the in-place layouts for
 // a single box only).
 hipError_t launch_moments(int lat, int dtype, const void* src, int layout, double* rho, double* u,
-                          const ChunkDesc* chunks, int nchunks, const BoxDesc* boxes, long long nsites, hipStream_t s);
+                          const ChunkDesc* chunks, int nchunks, int chunk_sites, const BoxDesc* boxes,
+                          long long nsites, hipStream_t s);
 hipError_t launch_totals(int lat, int dtype, const void* src, int layout, const ChunkDesc* chunks, int nchunks,
                          const int* box_chunk_begin, int nbox, const BoxDesc* boxes, double* partial, double* out,
                          hipStream_t s);

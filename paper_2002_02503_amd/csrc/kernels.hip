@@ -19,39 +19,75 @@ namespace lbm {
 
 // ---------------------------------------------------------------------------
 // Set-up, moments and reductions work on chunks: runs of consecutive sites
-// of one box, one block per chunk.
+// of one box.  The reductions take one block per chunk; set-up and moments one
+// thread per site, grid (chunks, blocks per chunk).
 // ---------------------------------------------------------------------------
 
-// Element index of population 0 of a site, relative to the box's first
-// element, in a layout of w-site blocks (BoxDesc): block local / w, position
-// local % w; population i is m(i) * w further on.
-__device__ __forceinline__ long long site_elem(long long local, int w, int Q)
+// Place of site k of a chunk: its block (for a single box its x-row) and its
+// position there, and for a single box y and z.  The chunk carries its first
+// site's place, so 32-bit divisions of x0 + k suffice (a 64-bit division of
+// the site index took some 100 instructions).
+struct SitePos {
+    long long row;
+    int x, y, z;
+};
+
+template <bool COORDS>
+__device__ __forceinline__ SitePos locate(const ChunkDesc& ch, int k, const BoxDesc& b)
 {
-    const long long r = local / w;
-    const long long x = local - r * w;
-    return r * Q * w + x;
+    const unsigned xx = unsigned(ch.x0) + unsigned(k);
+    const unsigned q = xx / unsigned(b.w);
+    SitePos p;
+    p.row = ch.row0 + q;
+    p.x = int(xx - q * unsigned(b.w));
+    p.y = p.z = 0;
+    if constexpr (COORDS) {
+        const unsigned yy = unsigned(ch.y0) + q;
+        const unsigned dz = yy / unsigned(b.ny);
+        p.y = int(yy - dz * unsigned(b.ny));
+        p.z = ch.z0 + int(dz);
+    }
+    return p;
 }
 
-// Element of population i of the site `local` of a single box (row tiles,
-// w = nx) when the state is in layout LAYOUT (StateLayout, internal.hpp):
-// natural: the site's own cell, tile row m(i); swapped: cell x + c_i, tile row
-// m(opp(i)); twisted: cell x + b_i (b_i the positive part of c_i), tile row
-// m(i) at even times and m(opp(i)) at odd times.
-template <class L, int LAYOUT, int I>
-__device__ __forceinline__ long long layout_elem(long long local, const BoxDesc& b)
+// Element of population 0 of a site in the natural layout (blocks of w sites,
+// BoxDesc); population i is m(i) * w further on.
+template <int Q>
+__device__ __forceinline__ long long site_elem(const SitePos& p, int w)
 {
-    const long long r = local / b.nx;
-    const int x = int(local - r * b.nx);
-    const int y = int(r % b.ny);
-    const int z = int(r / b.ny);
+    return p.row * Q * w + p.x;
+}
+
+// A site's wrapped neighbour coordinates, x + k - R at [k].
+template <class L>
+struct Around {
+    int x[2 * L::R + 1], y[2 * L::R + 1], z[2 * L::R + 1];
+
+    __device__ __forceinline__ Around(const SitePos& p, const BoxDesc& b)
+    {
+#pragma unroll
+        for (int k = 0; k <= 2 * L::R; ++k) {
+            x[k] = wrap_coord(p.x + k - L::R, b.nx);
+            y[k] = wrap_coord(p.y + k - L::R, b.ny);
+            z[k] = wrap_coord(p.z + k - L::R, b.nz);
+        }
+    }
+};
+
+// Element of population I of a site of a single box (row tiles, w = nx) when
+// the state is in layout LAYOUT (StateLayout, internal.hpp): swapped: cell
+// x + c_i, tile row m(opp(i)); twisted: cell x + b_i (b_i the positive part of
+// c_i), tile row m(i) at even times and m(opp(i)) at odd times.
+template <class L, int LAYOUT, int I>
+__device__ __forceinline__ long long layout_elem(const Around<L>& at, const BoxDesc& b)
+{
     const long long tile = (long long)L::Q * b.nx;
     constexpr bool SW = (LAYOUT == kSwapped);
-    constexpr int ox = SW ? L::c[I][0] : twist_offset<L>(I, 0);
-    constexpr int oy = SW ? L::c[I][1] : twist_offset<L>(I, 1);
-    constexpr int oz = SW ? L::c[I][2] : twist_offset<L>(I, 2);
+    constexpr int ox = L::R + (SW ? L::c[I][0] : twist_offset<L>(I, 0));
+    constexpr int oy = L::R + (SW ? L::c[I][1] : twist_offset<L>(I, 1));
+    constexpr int oz = L::R + (SW ? L::c[I][2] : twist_offset<L>(I, 2));
     constexpr int m = (LAYOUT == kTwistEven) ? mem_row<L>(I) : mem_row<L>(opp(I));
-    const int xs = wrap_coord(x + ox, b.nx), ys = wrap_coord(y + oy, b.ny), zs = wrap_coord(z + oz, b.nz);
-    return ((long long)zs * b.ny + ys) * tile + (long long)m * b.nx + xs;
+    return ((long long)at.z[oz] * b.ny + at.y[oy]) * tile + (long long)m * b.nx + at.x[ox];
 }
 
 // Initialisation: f := f^eq_K(rho, u) (eq. hermite), evaluated in double and
@@ -67,19 +103,26 @@ __global__ __launch_bounds__(256) void k_init(const double* __restrict__ rho, co
     const ChunkDesc ch = chunks[blockIdx.x];
     const BoxDesc b = boxes[ch.box];
     S* base = dst + b.mem;
-    for (int k = threadIdx.x; k < ch.count; k += blockDim.x) {
-        const long long s = ch.start + k;
-        const long long local = s - b.offset;
-        const long long e = site_elem(local, b.w, L::Q);
-        const double ux = u[s];
-        const double uy = u[nsites + s];
-        const double uz = (L::D == 3) ? u[2 * nsites + s] : 0.0;
-        double g[L::Q];
-        equilibrium_scaled<L, K, double>(rho[s] - 1.0, ux, uy, uz, g);
+    const int k = int(blockIdx.y) * int(blockDim.x) + int(threadIdx.x);
+    if (k >= ch.count) return;
+    const long long s = ch.start + k;
+    const SitePos pos = locate<LAYOUT != kNatural>(ch, k, b);
+    const double ux = u[s];
+    const double uy = u[nsites + s];
+    const double uz = (L::D == 3) ? u[2 * nsites + s] : 0.0;
+    double g[L::Q];
+    equilibrium_scaled<L, K>(rho[s] - 1.0, ux, uy, uz, g);
+    if constexpr (LAYOUT == kNatural) {
+        S* q = base + site_elem<L::Q>(pos, b.w);
         unroll<L::Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            if constexpr (LAYOUT == kNatural) ST::put_d(base + e + (long long)mem_row<L>(i) * b.w, g[i]);
-            else ST::put_d(base + layout_elem<L, LAYOUT, i>(local, b), g[i]);
+            ST::put_d(q + (long long)mem_row<L>(i) * b.w, g[i]);
+        });
+    } else {
+        const Around<L> at(pos, b);
+        unroll<L::Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            ST::put_d(base + layout_elem<L, LAYOUT, i>(at, b), g[i]);
         });
     }
 }
@@ -104,42 +147,44 @@ __device__ __forceinline__ void site_moments(const S* __restrict__ p, int w, dou
         if constexpr (cz != 0) j[2] += double(cz) * gi;
     });
     // stored units are 1/S of a population
-    dsum /= double(L::S);
-    j[0] /= double(L::S);
-    j[1] /= double(L::S);
-    j[2] /= double(L::S);
+    dsum = over<L::S>(dsum);
+    j[0] = over<L::S>(j[0]);
+    j[1] = over<L::S>(j[1]);
+    if constexpr (L::D == 3) j[2] = over<L::S>(j[2]);
 }
 
 // The same for a single box whose state is in one of the in-place steps'
-// layouts (layout_elem).  `local` is the site's index inside its box.
+// layouts (layout_elem).
 template <class L, class S, int LAYOUT>
-__device__ __forceinline__ void relaid_site_moments(const S* __restrict__ base, long long local, const BoxDesc& b,
+__device__ __forceinline__ void relaid_site_moments(const S* __restrict__ base, const SitePos& pos, const BoxDesc& b,
                                                     double& dsum, double (&j)[3])
 {
     using ST = Store<S>;
+    const Around<L> at(pos, b);
     dsum = 0.0;
     j[0] = j[1] = j[2] = 0.0;
     unroll<L::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-        const double gi = double(ST::get(base + layout_elem<L, LAYOUT, i>(local, b)));
+        const double gi = double(ST::get(base + layout_elem<L, LAYOUT, i>(at, b)));
         dsum += gi;
         if constexpr (cx != 0) j[0] += double(cx) * gi;
         if constexpr (cy != 0) j[1] += double(cy) * gi;
         if constexpr (cz != 0) j[2] += double(cz) * gi;
     });
-    dsum /= double(L::S);
-    j[0] /= double(L::S);
-    j[1] /= double(L::S);
-    j[2] /= double(L::S);
+    dsum = over<L::S>(dsum);
+    j[0] = over<L::S>(j[0]);
+    j[1] = over<L::S>(j[1]);
+    if constexpr (L::D == 3) j[2] = over<L::S>(j[2]);
 }
 
 template <class L, class S, int LAYOUT>
-__device__ __forceinline__ void stored_site_moments(const S* __restrict__ base, long long local, const BoxDesc& b,
-                                                    double& dsum, double (&j)[3])
+__device__ __forceinline__ void stored_site_moments(const S* __restrict__ base, const ChunkDesc& ch, int k,
+                                                    const BoxDesc& b, double& dsum, double (&j)[3])
 {
-    if constexpr (LAYOUT != kNatural) relaid_site_moments<L, S, LAYOUT>(base, local, b, dsum, j);
-    else site_moments<L, S>(base + site_elem(local, b.w, L::Q), b.w, dsum, j);
+    const SitePos pos = locate<LAYOUT != kNatural>(ch, k, b);
+    if constexpr (LAYOUT != kNatural) relaid_site_moments<L, S, LAYOUT>(base, pos, b, dsum, j);
+    else site_moments<L, S>(base + site_elem<L::Q>(pos, b.w), b.w, dsum, j);
 }
 
 template <class L, class S, int LAYOUT>
@@ -150,15 +195,15 @@ __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ src, doub
     const ChunkDesc ch = chunks[blockIdx.x];
     const BoxDesc b = boxes[ch.box];
     const S* base = src + b.mem;
-    for (int k = threadIdx.x; k < ch.count; k += blockDim.x) {
-        const long long s = ch.start + k;
-        double d, j[3];
-        stored_site_moments<L, S, LAYOUT>(base, s - b.offset, b, d, j);
-        const double r = 1.0 + d;
-        rho[s] = r;
+    const int k = int(blockIdx.y) * int(blockDim.x) + int(threadIdx.x);
+    if (k >= ch.count) return;
+    const long long s = ch.start + k;
+    double d, j[3];
+    stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
+    const double r = 1.0 + d;
+    rho[s] = r;
 #pragma unroll
-        for (int a = 0; a < L::D; ++a) u[a * nsites + s] = j[a] / r;
-    }
+    for (int a = 0; a < L::D; ++a) u[a * nsites + s] = j[a] / r;
 }
 
 // ---------------------------------------------------------------------------
@@ -200,7 +245,7 @@ __global__ __launch_bounds__(kRedBlock) void k_totals_partial(const S* __restric
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int k = threadIdx.x; k < ch.count; k += kRedBlock) {
         double d, j[3];
-        stored_site_moments<L, S, LAYOUT>(base, ch.start + k - b.offset, b, d, j);
+        stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
         acc[0] += d;
         acc[1] += j[0];
         acc[2] += j[1];
@@ -248,7 +293,7 @@ __global__ __launch_bounds__(kRedBlock) void k_residual_partial(const S* __restr
     for (int k = threadIdx.x; k < ch.count; k += kRedBlock) {
         const long long s = ch.start + k;
         double d, j[3];
-        stored_site_moments<L, S, LAYOUT>(base, s - b.offset, b, d, j);
+        stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
         const double r = 1.0 + d;
 #pragma unroll
         for (int a = 0; a < L::D; ++a) {
@@ -313,30 +358,34 @@ static hipError_t by_layout(int layout, F&& f)
 }
 
 hipError_t launch_init(int lat, int dtype, int K, int layout, const double* rho, const double* u, void* dst,
-                       const ChunkDesc* chunks, int nchunks, const BoxDesc* boxes, long long nsites, hipStream_t s)
+                       const ChunkDesc* chunks, int nchunks, int chunk_sites, const BoxDesc* boxes,
+                       long long nsites, hipStream_t s)
 {
     if (layout != kNatural && layout != kTwistEven) return hipErrorInvalidValue;
     return dispatch(lat, dtype, K, [&](auto Lt, auto* Sp, auto Kc) -> hipError_t {
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
         constexpr int KK = decltype(Kc)::value;
+        const dim3 grid(unsigned(nchunks), unsigned((chunk_sites + 255) / 256));
         if (layout == kTwistEven)
-            k_init<L, S, KK, kTwistEven><<<nchunks, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites);
+            k_init<L, S, KK, kTwistEven><<<grid, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites);
         else
-            k_init<L, S, KK, kNatural><<<nchunks, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites);
+            k_init<L, S, KK, kNatural><<<grid, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_moments(int lat, int dtype, const void* src, int layout, double* rho, double* u,
-                          const ChunkDesc* chunks, int nchunks, const BoxDesc* boxes, long long nsites, hipStream_t s)
+                          const ChunkDesc* chunks, int nchunks, int chunk_sites, const BoxDesc* boxes,
+                          long long nsites, hipStream_t s)
 {
+    const dim3 grid(unsigned(nchunks), unsigned((chunk_sites + 255) / 256));
     return dispatch_ld(lat, dtype, [&](auto Lt, auto* Sp, auto) -> hipError_t {
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
         return by_layout(layout, [&](auto Lay) -> hipError_t {
             constexpr int LAY = decltype(Lay)::value;
-            k_moments<L, S, LAY><<<nchunks, 256, 0, s>>>(static_cast<const S*>(src), rho, u, chunks, boxes, nsites);
+            k_moments<L, S, LAY><<<grid, 256, 0, s>>>(static_cast<const S*>(src), rho, u, chunks, boxes, nsites);
             return hipGetLastError();
         });
     });
@@ -401,11 +450,12 @@ __global__ __launch_bounds__(256) void k_relayout(const S* __restrict__ src, S* 
     const int z = blockIdx.z;
     const int x = int(blockIdx.x) * int(blockDim.x) + int(threadIdx.x);
     if (x >= b.nx) return;
-    const long long local = ((long long)z * b.ny + y) * b.nx + x;
-    const long long nat = site_elem(local, b.nx, L::Q);
+    const SitePos pos{(long long)z * b.ny + y, x, y, z};
+    const long long nat = site_elem<L::Q>(pos, b.nx);
+    const Around<L> at(pos, b);
     unroll<L::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        const long long e = layout_elem<L, LAYOUT, i>(local, b);
+        const long long e = layout_elem<L, LAYOUT, i>(at, b);
         const long long n = nat + (long long)mem_row<L>(i) * b.nx;
         if constexpr (TO_NATURAL) dst[n] = src[e];
         else dst[e] = src[n];
