@@ -612,28 +612,43 @@ __device__ __forceinline__ void collide_site(R (&G)[L::Q], R omega, R theta)
                                                 sxz, syz);
 }
 
-// Equilibrium in stored units, G_i = S (f^eq_i - w_i) (eq. hermite truncated at K).
+// Equilibrium in stored units, G_i = S (f^eq_i - w_i) (eq. hermite truncated at
+// K).  The terms of an opposite pair differ in the sign of the odd ones only,
+// so they are evaluated once.
 template <class L, int K>
 __device__ __forceinline__ void equilibrium_scaled(double drho, double ux, double uy, double uz, double (&G)[L::Q])
 {
     using R = double;
     constexpr R IT0 = R(L::INV_T0);
     const R v = (ux * ux + uy * uy + uz * uz) * IT0;
-    unroll<L::Q>([&](auto I) {
+    auto pair = [&](auto I, R& Ep, R& Em) {
         constexpr int i = decltype(I)::value;
         constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-        constexpr R Wi = R(L::W[i]);
         const R a = (R(cx) * ux + R(cy) * uy + R(cz) * uz) * IT0;
-        R hm1 = R(1), h = a, E = a;
+        R hm1 = R(1), h = a;
+        Ep = a;
+        Em = -a;
         unroll<K - 1>([&](auto N) {
             constexpr int n = decltype(N)::value + 1;
             constexpr int fact[] = {1, 1, 2, 6, 24, 120};
             const R hn = a * h - R(n) * v * hm1;
             hm1 = h;
             h = hn;
-            E += over<fact[n + 1]>(h);
+            const R t = over<fact[n + 1]>(h);
+            Ep += t;
+            Em += (n % 2 == 0) ? -t : t;
         });
-        G[i] = Wi * (drho * (R(1) + E) + E);
+    };
+    R Ep, Em;
+    pair(std::integral_constant<int, 0>{}, Ep, Em);
+    G[0] = R(L::W[0]) * (drho * (R(1) + Ep) + Ep);
+    unroll<(L::Q - 1) / 2>([&](auto P) {
+        constexpr int i = 2 * decltype(P)::value + 1;
+        constexpr R Wi = R(L::W[i]);
+        R Ep, Em;
+        pair(std::integral_constant<int, i>{}, Ep, Em);
+        G[i] = Wi * (drho * (R(1) + Ep) + Ep);
+        G[i + 1] = Wi * (drho * (R(1) + Em) + Em);
     });
 }
 
