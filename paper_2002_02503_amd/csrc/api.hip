@@ -117,6 +117,7 @@ struct lbm_ctx {
     ChunkDesc* d_chunks = nullptr;
     int nchunks = 0;
     int chunk_sites = kChunkSites;
+    TilePlan tile{};                // plan of the tile kernel (steps = 0: none)
     int* d_box_chunk_begin = nullptr;
     double* d_partial = nullptr;
     double* d_out = nullptr;
@@ -147,11 +148,34 @@ int step_kind(const lbm_ctx* h)
     return h->theta != 0.0 ? kFilteredQ : kFiltered;
 }
 
+// The two-step kernel applies to this box (host.hpp, two_step_fits).
+bool two_step_ok(const lbm_ctx* h)
+{
+    return is_single(h) && two_step_fits(h->lat, h->dtype, h->dims[0], h->dims[1], h->dims[2]);
+}
+// The tile kernel has a plan for this box.
+bool tile_ok(const lbm_ctx* h) { return is_single(h) && h->tile.steps > 0; }
+
+// Without a choice by the caller or the tuner: the tile kernel where it has a
+// plan; the two-step kernel in FP32 and FP64 from two column-planes per compute
+// unit on (D3Q19 FP32, us per step, one-site against two-step: 64^3 8.5 / 7.3,
+// 128^3 53.2 / 36.6, 256^3 422 / 247; 16-bit storage at 128^3 26 / 32); else the
+// one-site step, also where the caller set a launch shape, which is that
+// step's.
+int auto_kernel(const lbm_ctx* h)
+{
+    if (h->block > 0 || h->grid > 0) return LBM_KERNEL_SCALAR;
+    if (tile_ok(h)) return LBM_KERNEL_TILE;
+    if (h->elem >= 4 && two_step_ok(h) &&
+        h->nsites / (kTwoStepTileX * two_step_tile_y(h->elem)) >= 2 * int64_t(h->cus))
+        return LBM_KERNEL_TWO_STEP;
+    return LBM_KERNEL_SCALAR;
+}
+
 int effective_kernel(const lbm_ctx* h)
 {
     if (!is_single(h)) return LBM_KERNEL_SCALAR;
-    if (h->kernel == LBM_KERNEL_AUTO) return LBM_KERNEL_SCALAR;  // measured faster unless tuned otherwise
-    return h->kernel;
+    return h->kernel == LBM_KERNEL_AUTO ? auto_kernel(h) : h->kernel;
 }
 
 int effective_block(const lbm_ctx* h)
@@ -384,6 +408,7 @@ lbm_status create_common(lbm_t* out, int32_t lattice, int32_t nbox, const int64_
                 hipSuccess)
                 return cleanup(fail_hip(e, "copy boxes"));
         }
+        if (nbox == 1 && !tile_plan(L, dtype, dims[0], dims[1], dims[2], h->cus, &h->tile)) h->tile = TilePlan{};
         *out = h;
         return LBM_OK;
     } catch (...) {
@@ -426,13 +451,10 @@ bool twisted(const lbm_ctx* h) { return is_single(h) && effective_kernel(h) == L
 // The step works inside one buffer (either in-place form).
 bool one_buffer(const lbm_ctx* h) { return in_place(h) || twisted(h); }
 
-// The two-step kernel applies to this box (host.hpp, two_step_fits) / is the
-// one in use.
-bool two_step_ok(const lbm_ctx* h)
-{
-    return is_single(h) && two_step_fits(h->lat, h->dtype, h->dims[0], h->dims[1], h->dims[2]);
-}
+// The two-step / tile kernel is the one in use.
 bool two_step(const lbm_ctx* h) { return is_single(h) && effective_kernel(h) == LBM_KERNEL_TWO_STEP; }
+
+bool tiled(const lbm_ctx* h) { return is_single(h) && effective_kernel(h) == LBM_KERNEL_TILE; }
 
 // Blocks of the two-step kernel: the chosen grid, else one per compute unit
 // (its LDS planes leave room for one block per CU; measured fastest).
@@ -522,17 +544,50 @@ hipError_t launch_two(lbm_ctx* h, int parity, hipStream_t s)
                         1.0 - 1.0 / h->tau[0], h->theta, grid, s);
 }
 
-// Steps the next launch takes when `left` remain: two for the two-step kernel
-// (an odd last step goes to the one-site step), else one.
-int steps_in_launch(const lbm_ctx* h, int64_t left) { return (two_step(h) && left >= 2) ? 2 : 1; }
+// k >= 2 steps in one launch on tiles (step_tile.hpp), likewise.
+hipError_t launch_tile(lbm_ctx* h, int parity, int k, hipStream_t s)
+{
+    TileGeom geo;
+    geo.nx = int(h->dims[0]);
+    geo.ny = int(h->dims[1]);
+    geo.nz = int(h->dims[2]);
+    geo.tx = h->tile.tx;
+    geo.ty = h->tile.ty;
+    geo.tz = h->tile.tz;
+    geo.steps = k;
+    geo.block = h->tile.block;
+    geo.cap = int(tile_region(h->lat, h->tile, h->dims[0], k));
+    return launch_step_tile(h->lattice, h->dtype, h->K, step_kind(h), h->buf[parity], h->buf[parity ^ 1], geo,
+                            1.0 - 1.0 / h->tau[0], h->theta, s);
+}
+
+// Most steps of one launch.
+int launch_steps_max(const lbm_ctx* h) { return two_step(h) ? 2 : tiled(h) ? h->tile.steps : 1; }
+
+// Steps the next launch takes when `left` remain (a single last one goes to
+// the one-site step).
+int steps_in_launch(const lbm_ctx* h, int64_t left) { return int(std::min<int64_t>(left, launch_steps_max(h))); }
 
 hipError_t launch_steps(lbm_ctx* h, int parity, int k, hipStream_t s)
 {
-    return k == 2 ? launch_two(h, parity, s) : launch_one(h, parity, s);
+    if (k == 1) return launch_one(h, parity, s);
+    return tiled(h) ? launch_tile(h, parity, k, s) : launch_two(h, parity, s);
 }
 
 // Launches that take n steps; each flips the buffer parity.
-int64_t launches_for(const lbm_ctx* h, int64_t n) { return two_step(h) ? n / 2 + n % 2 : n; }
+int64_t launches_for(const lbm_ctx* h, int64_t n)
+{
+    const int m = launch_steps_max(h);
+    return n / m + (n % m != 0);
+}
+
+// Steps of one captured graph: the handle's chunk, for the tile kernel cut to
+// whole launches.
+int graph_steps(const lbm_ctx* h)
+{
+    const int m = launch_steps_max(h);
+    return (tiled(h) && h->graph_chunk > m) ? h->graph_chunk - h->graph_chunk % m : h->graph_chunk;
+}
 
 // Where the current state is, and in which layout (StateLayout).
 void state_view(const lbm_ctx* h, const void** state, int* layout)
@@ -593,7 +648,7 @@ void relayout_host(const lbm_ctx* h, int layout, bool to_natural, const char* sr
 
 lbm_status build_graph(lbm_ctx* h, int parity)
 {
-    const int n = h->graph_chunk;
+    const int n = graph_steps(h);
     if (h->gexec[parity] && h->gexec_steps[parity] == n) return LBM_OK;
     if (h->gexec[parity]) {
         (void)hipGraphExecDestroy(h->gexec[parity]);
@@ -800,13 +855,15 @@ lbm_status lbm_set_kernel(lbm_t h, int32_t kernel)
         if (lbm_status st = check_handle(h)) return st;
         if (kernel != LBM_KERNEL_AUTO && kernel != LBM_KERNEL_SCALAR && kernel != LBM_KERNEL_ROW_WAVE &&
             kernel != LBM_KERNEL_IN_PLACE && kernel != LBM_KERNEL_TWO_ROW && kernel != LBM_KERNEL_TWIST &&
-            kernel != LBM_KERNEL_TWO_STEP)
+            kernel != LBM_KERNEL_TWO_STEP && kernel != LBM_KERNEL_TILE)
             return fail(LBM_EINVAL, "unknown kernel variant %d", kernel);
         if (kernel == LBM_KERNEL_TWO_STEP && !two_step_ok(h))
             return fail(LBM_EINVAL,
                         "the two-step kernel needs a single D3Q15 or D3Q19 box with nx a multiple of %d, ny a "
                         "multiple of %d and one z-plane of populations below 2 GiB",
                         kTwoStepTileX, two_step_tile_y(h->elem));
+        if (kernel == LBM_KERNEL_TILE && !tile_ok(h))
+            return fail(LBM_EINVAL, "the tile kernel needs a single D2Q9, D3Q15 or D3Q19 box for which it has a plan");
         if ((kernel == LBM_KERNEL_IN_PLACE || kernel == LBM_KERNEL_TWIST) && !is_single(h))
             return fail(LBM_EINVAL, "the in-place steps are for a single box; batches use the tiled batched kernel");
         if (kernel == LBM_KERNEL_TWO_ROW && (!is_single(h) || h->dims[1] % 2 != 0))
@@ -891,7 +948,7 @@ lbm_status lbm_step(lbm_t h, int64_t n)
         if (!one_buffer(h))
             if (lbm_status st = ensure_second(h)) return st;
         if (lbm_status st = build_tiles(h)) return st;
-        const int G = h->graph_chunk;
+        const int G = graph_steps(h);
         int64_t left = n;
         if (G > 1) {
             while (left >= G) {
@@ -959,7 +1016,8 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
         LaunchChoice best;
         if (tune_cache_lookup(cache_path, key, &best)) {
             // the cache is a text file: take only values this library can launch
-            if (best.kernel < LBM_KERNEL_AUTO || best.kernel > LBM_KERNEL_TWO_STEP) best.kernel = LBM_KERNEL_SCALAR;
+            if (best.kernel < LBM_KERNEL_AUTO || best.kernel > LBM_KERNEL_TILE) best.kernel = LBM_KERNEL_SCALAR;
+            if (best.kernel == LBM_KERNEL_TILE && !tile_ok(h)) best.kernel = LBM_KERNEL_SCALAR;
             if (best.kernel == LBM_KERNEL_TWO_STEP && !two_step_ok(h)) best.kernel = LBM_KERNEL_SCALAR;
             if (!(best.block == 0 || (best.block >= 64 && best.block <= 256 && best.block % 64 == 0))) best.block = 0;
             if (best.grid < 0) best.grid = 0;
@@ -993,6 +1051,7 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
                 cand.push_back({LBM_KERNEL_TWO_STEP, 0, 0});
                 cand.push_back({LBM_KERNEL_TWO_STEP, 0, 2 * h->cus});
             }
+            if (tile_ok(h)) cand.push_back({LBM_KERNEL_TILE, 0, 0});
         } else {
             for (int b : {64, 128, 256})
                 for (int g : {0, 1024, 2048, 4096}) cand.push_back({LBM_KERNEL_SCALAR, b, g});

@@ -2,9 +2,11 @@
 // builds and runs under the host sanitizers.
 #include "host.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <cstdlib>
 #include <fstream>
 #include <sstream>
 
@@ -107,6 +109,73 @@ bool two_step_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int6
     if (nx % kTwoStepTileX != 0 || ny % two_step_tile_y(elem) != 0) return false;
     const uint64_t plane_sites = uint64_t(nx) * uint64_t(ny);  // below 2^62
     return plane_sites <= ((uint64_t(1) << 31) - 1) / (uint64_t(L.Q) * elem);
+}
+
+int64_t tile_region(const LatticeInfo& L, const TilePlan& p, int64_t nx, int steps)
+{
+    const int64_t g = 2 * (steps - 1);
+    return (p.tx + (p.tx == nx ? 0 : g)) * (p.ty + g) * (L.D == 3 ? p.tz + g : 1);
+}
+
+bool tile_plan_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, const TilePlan& p)
+{
+    const int64_t elem = int64_t(storage_bytes(dtype));
+    if (L.R != 1 || elem == 0 || nx < 1 || ny < 1 || nz < 1) return false;
+    if (p.tx < 1 || p.ty < 1 || p.tz < 1 || p.tx > nx || p.ty > ny || p.tz > nz) return false;
+    if (p.steps < 2 || p.steps > kTileMaxSteps || p.block < 64 || p.block > 1024 || p.block % 64 != 0) return false;
+    if (L.D == 2 && nz != 1) return false;
+    const int64_t n[3] = {nx, ny, nz};
+    for (int a = 0; a < L.D; ++a)
+        if (n[a] > 2 && p.steps - 1 > n[a]) return false;
+    if (p.tx > 1024 || p.ty > 1024 || p.tz > 1024) return false;
+    if (tile_region(L, p, nx, p.steps) * L.Q * elem > kTileMaxLds) return false;
+    if (tile_region(L, p, nx, p.steps - 1) > p.block) return false;
+    const int64_t limit = int64_t(1) << 32;
+    if (nx > limit / (L.Q * elem) / ny / nz) return false;
+    return true;
+}
+
+// n cut into pieces of at most `most`, of nearly equal size.
+static int even_piece(int64_t n, int64_t most)
+{
+    const int64_t pieces = (n + most - 1) / most;
+    return int((n + pieces - 1) / pieces);
+}
+
+bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, int cus, TilePlan* out)
+{
+    if (L.R != 1 || nx < 1 || ny < 1 || nz < 1 || cus < 1) return false;
+    if (nx > kMaxSites / ny / nz) return false;
+    const int64_t share = nx * ny * nz / cus;  // sites of a compute unit
+    TilePlan p{1, 1, 1, 0, 0};
+    if (L.D == 2) {
+        // a tile per compute unit while the box is small, then 32 x 16
+        p.tx = even_piece(nx, share <= 32 ? 8 : share <= 128 ? 16 : 32);
+        p.ty = even_piece(ny, share <= 32 ? 4 : share <= 256 ? 8 : 16);
+        p.steps = share <= 256 ? 8 : 5;
+    } else {
+        if (share > kTileShare3d) return false;
+        p.tx = even_piece(nx, 64);
+        while (int64_t(p.tx) * p.ty * p.tz < share) {
+            int& side = p.ty <= p.tz ? p.ty : p.tz;
+            if (2 * side > (p.ty <= p.tz ? ny : nz)) break;
+            side *= 2;
+        }
+        p.steps = share <= 32 ? 3 : 2;
+    }
+    // fewer steps where the box is narrower than the ring or LDS too small
+    for (; p.steps >= 2; --p.steps) {
+        const int64_t n = tile_region(L, p, nx, p.steps);
+        const int64_t rounds = (n + 1023) / 1024;
+        const int64_t least = tile_region(L, p, nx, p.steps - 1);
+        const int64_t threads = std::max(least, (n + rounds - 1) / rounds);
+        p.block = int(std::min<int64_t>(1024, (threads + 63) / 64 * 64));
+        if (tile_plan_fits(L, dtype, nx, ny, nz, p)) {
+            *out = p;
+            return true;
+        }
+    }
+    return false;
 }
 
 uint64_t geometry_hash(const std::vector<int64_t>& dims)

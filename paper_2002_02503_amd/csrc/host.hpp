@@ -57,6 +57,41 @@ constexpr int two_step_tile_y(size_t elem) { return elem == 8 ? 4 : 8; }
 // 32 bits.
 bool two_step_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz);
 
+constexpr int kTileMaxSteps = 16;
+constexpr int64_t kTileMaxLds = 160 * 1024;  // a compute unit's LDS
+
+// Plan of the tile kernel (step_tile.hpp): tile tx x ty x tz, `steps` steps a
+// launch, blocks of `block` threads.
+struct TilePlan {
+    int tx, ty, tz, steps, block;
+};
+
+// Sites of step 1's region of a full tile, for `steps` steps (no ring in x when
+// the tile holds whole x-rows).
+int64_t tile_region(const LatticeInfo& L, const TilePlan& p, int64_t nx, int steps);
+
+// Whether the plan runs on an nx x ny x nz box: a one-site ring per step, the
+// region of step 1 in LDS, that of step 2 with one thread per site, ring
+// coordinates within one period of the box (any for one and two sites) and
+// the state below 4 GiB (offsets are formed in 32 bits).
+bool tile_plan_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, const TilePlan& p);
+
+// The plan for a box on a device of `cus` compute units; false: none, because
+// none fits or the one-site step is faster.
+//   - D2Q9: every size.  Measured, us per step, one-site against the plan (tile,
+//     steps): 64^2 FP64 2.52 / 0.96 (8 x 4, 8), 256^2 FP32 3.29 / 1.65 (32 x 8,
+//     8), 601 x 400 FP32 5.9 / 3.2 (32 x 16, 5), 1024^2 FP32 14.4 / 8.0 and
+//     FP64 26.5 / 10.4 (32 x 16, 5).
+//   - D3Q15 and D3Q19: up to kTileShare3d sites per compute unit.  The ring
+//     costs more in three dimensions, so two steps (three up to 32 sites per
+//     unit) and whole x-rows, whose loads use full lines: 16^3 FP32 3.09 / 1.91
+//     (16 x 2 x 1, 3), 32^3 FP32 3.64 / 2.85 (32 x 2 x 2, 2), FP64 4.48 / 3.86,
+//     40 x 37 x 29 4.52 / 4.28; at 64^3 (8.5 / 8.4) and above nothing is gained.
+// Block: step 1's region in as few rounds as 1024 threads allow (32^3 with the
+// threads that step 2 needs, 128, took 4.0 us per step).
+constexpr int64_t kTileShare3d = 160;
+bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, int cus, TilePlan* out);
+
 // The argument checks of lbm_create / lbm_create_batch for nbox boxes
 // (dims: nbox * 3, tau: nbox).  True when every box is valid; otherwise false
 // with the reason in *why.

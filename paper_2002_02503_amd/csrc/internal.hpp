@@ -40,6 +40,17 @@ struct Step2Geom {
     int xcd_order;        // 1: consecutive columns on one XCD (grid a multiple of 8)
 };
 
+// Single box, several steps per launch in LDS (step_tile.hpp): tiles of tx x ty
+// x tz sites, `steps` steps, blocks of `block` threads; cap: region sites of
+// step 1, (tx + 2 (steps - 1)) ... of a full tile.
+struct TileGeom {
+    int nx, ny, nz;
+    int tx, ty, tz;
+    int steps;
+    int block;
+    int cap;
+};
+
 // Single box, row-wave form: each lane owns V consecutive sites of an x-row,
 // a row takes lanes_per_row = nx / V lanes and a 64-lane wavefront holds
 // rows_per_wave = 64 / lanes_per_row rows.
@@ -115,6 +126,10 @@ hipError_t launch_step_tw(int lat, int dtype, int K, int kind, void* buf, bool e
 // blocks; D3Q15 and D3Q19 only (two_step_fits), else hipErrorInvalidValue.
 hipError_t launch_step2(int lat, int dtype, int K, int kind, const void* src, void* dst, const Step2Geom& geo,
                         double omega, double theta, int grid, hipStream_t s);
+// Several steps in one launch on tiles in LDS (step_tile.hpp, k_step_tile), from
+// src to dst; D2Q9, D3Q15 and D3Q19 only, else hipErrorInvalidValue.
+hipError_t launch_step_tile(int lat, int dtype, int K, int kind, const void* src, void* dst, const TileGeom& geo,
+                            double omega, double theta, hipStream_t s);
 // A single box's state from `layout` to the natural layout (to_natural) or
 // back, into another buffer (bit-exact permutation).
 hipError_t launch_relayout(int lat, int dtype, int layout, bool to_natural, const void* src, void* dst,

@@ -534,6 +534,19 @@ hipError_t launch_step2(int lat, int dtype, int K, int kind, const void* src, vo
     });
 }
 
+hipError_t launch_step_tile(int lat, int dtype, int K, int kind, const void* src, void* dst, const TileGeom& geo,
+                            double omega, double theta, hipStream_t s)
+{
+    return by_pair(lat, dtype, [&](auto Lt, auto* Sp) -> hipError_t {
+        using L = decltype(Lt);
+        using S = std::remove_pointer_t<decltype(Sp)>;
+        if constexpr (L::R == 1)
+            return launch_step_tile_l<L, S>(K, kind, src, dst, geo, omega, theta, s);
+        else
+            return hipErrorInvalidValue;
+    });
+}
+
 int vec_sites_per_lane(int lat, int dtype)
 {
     int v = 0;
