@@ -88,12 +88,13 @@ def timed_steps(sim, steps: int, warmup: int) -> float:
     return e0.elapsed_time(e1) / steps
 
 
-KERNEL_NAMES = {1: "scalar", 2: "row_wave", 3: "in_place", 4: "two_row", 5: "twist", 6: "two_step", 7: "tile"}
+KERNEL_NAMES = {1: "scalar", 2: "row_wave", 3: "in_place", 4: "two_row", 5: "twist", 6: "two_step", 7: "tile", 8: "columns"}
 KERNEL_SYMBOLS = {"scalar": "k_step", "row_wave": "k_step_vec", "in_place": "k_step_ip", "two_row": "k_step_pair",
-                  "twist": "k_step_tw", "two_step": "k_step2", "tile": "k_step_tile"}
+                  "twist": "k_step_tw", "two_step": "k_step2", "tile": "k_step_tile",
+                  "columns": "k_step2"}
 # time steps one launch of a kernel takes (the two-step kernel: two; per-launch
 # figures count both)
-STEPS_PER_LAUNCH = {"two_step": 2}
+STEPS_PER_LAUNCH = {"two_step": 2, "columns": 2}
 STORAGE_CTYPE = {"fp64": "double", "fp32": "float", "fp16": "_Float16", "bf16": "bf16_t"}
 
 

@@ -70,8 +70,8 @@ typedef enum {
 /* Step-kernel variants for a single box (lbm_set_kernel). */
 typedef enum {
     LBM_KERNEL_AUTO = 0,      /* until a tuned choice is set: the tile kernel where it applies, in FP32 and FP64
-                                 the two-step kernel where it applies and the box is large enough to gain
-                                 (from about 64^3), else the scalar step, also where a launch shape was set */
+                                 the two-step kernel (on columns of any size where nx and ny do not fit it)
+                                 where the box is large enough to gain (64^3; 400,000 sites), else the scalar step, also where a launch shape was set */
     LBM_KERNEL_SCALAR = 1,    /* one site per thread, 4/8-byte accesses */
     LBM_KERNEL_ROW_WAVE = 2,  /* V sites per lane, 8/16-byte accesses, x-neighbours by lane shuffle */
     LBM_KERNEL_IN_PLACE = 3,  /* one site per thread on one buffer: each step reads and writes the same
@@ -87,9 +87,10 @@ typedef enum {
                                  in z, takes the first step on the column and a one-site ring around it
                                  and keeps that state in LDS for the second, so the state is read and
                                  written once per two steps (bit-identical results) */
-    LBM_KERNEL_TILE = 7       /* several steps per launch (D2Q9, D3Q15, D3Q19; small boxes): a block takes
+    LBM_KERNEL_TILE = 7,      /* several steps per launch (D2Q9, D3Q15, D3Q19; small boxes): a block takes
                                  them on a tile of the box in LDS, each step on a ring of sites one
                                  narrower than the last (bit-identical results) */
+    LBM_KERNEL_COLUMNS = 8    /* LBM_KERNEL_TWO_STEP on columns of any size: no condition on nx and ny */
 } lbm_kernel;
 
 typedef struct {
@@ -224,6 +225,8 @@ lbm_status lbm_set_launch(lbm_t h, int32_t block, int32_t grid);
  * 64, ny a multiple of 8 (4 for FP64 storage) and one z-plane of populations
  * (Q nx ny values) below 2 GiB, else LBM_EINVAL.  An odd step count ends with
  * one step of the scalar kernel; the state stays in the natural layout.
+ * LBM_KERNEL_COLUMNS needs a single D3Q15 or D3Q19 box with one z-plane of
+ * populations below 2 GiB, else LBM_EINVAL.
  * LBM_KERNEL_TILE needs a single D2Q9, D3Q15 or D3Q19 box whose state is below
  * 4 GiB (D2Q9 of any other size; in 3-D at most 160 sites per compute unit),
  * else LBM_EINVAL.  The library chooses the tile and the steps per launch; the
@@ -238,11 +241,11 @@ lbm_status lbm_set_kernel(lbm_t h, int32_t kernel);
 /* Autotune the step's launch: time every candidate over `steps` steps with HIP
  * events, in three interleaved rounds, and keep the candidate with the fastest
  * round.  Single box: the scalar step at 64/128/256 threads per block, the
- * in-place, twist and two-row (ny even) steps at 256, the scalar, in-place
- * and twist steps at one whole x-row per block when nx rounds up to 192 lanes,
- * the row-wave step where it applies, and the two-step kernel (where it
- * applies) at one and at two blocks per compute unit, and the tile kernel where
- * it applies.  Batch: 64/128/256 threads per block, with
+ * in-place and twist steps at 256, all three at one whole x-row per block when
+ * nx rounds up to 192 lanes, and either the tile kernel, or the two-step kernel
+ * (on columns of any size where nx and ny do not fit it) at one and at two
+ * blocks per compute unit, or, where neither applies, the two-row (ny even) and
+ * row-wave steps.  Batch: 64/128/256 threads per block, with
  * one wave per 64-site block of the layout or 1024/2048/4096 persistent
  * blocks.  The state is saved before and restored after, so t and the
  * populations are unchanged (all candidates compute the same bits).  Choices are appended to the text file `cache_path` (NULL: the

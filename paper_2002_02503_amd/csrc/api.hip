@@ -63,6 +63,20 @@ constexpr int kManyChunks = 2048;
 constexpr int kDefaultGraphChunk = 32;
 constexpr int kTuneRounds = 3;
 
+// Size of one state buffer for which the two-step kernel's stores are cached:
+// both buffers then fit the 256 MB Infinity Cache, where the next launch finds
+// them, and the state is past the 32 MB of L2, whose dirty lines a launch has to
+// write back when it ends.  Measured, us per step of D3Q19 FP32, non-temporal
+// against cached: 64^3 (20 MB) 7.3 / 7.9, 96^3 (67 MB) 18.0 / 15.9, 100^3 (76 MB)
+// 20.9 / 17.4, 256 x 256 x 16 (80 MB) 19.3 / 16.7, 128^3 (159 MB) 36.6 / 38.9,
+// 160^3 (311 MB) 83 / 85-102.
+constexpr size_t kCachedStoresFrom = size_t(40) << 20;
+constexpr size_t kCachedStoresTo = size_t(128) << 20;
+
+// Smallest boxes for which the default takes the two-step kernel (auto_kernel).
+constexpr int64_t kTwoStepSites = 64 * 64 * 64;
+constexpr int64_t kColumnsSites = 400000;
+
 // Scratch of the allocation-free residual (lbm_residual_noalloc): the
 // per-chunk partial sums of the residual kernels, 4 doubles per reduction
 // chunk.  Every GPU the library runs on holds its own copy of this array for
@@ -153,22 +167,30 @@ bool two_step_ok(const lbm_ctx* h)
 {
     return is_single(h) && two_step_fits(h->lat, h->dtype, h->dims[0], h->dims[1], h->dims[2]);
 }
+// The same kernel on columns of any size (host.hpp, columns_fit).
+bool columns_ok(const lbm_ctx* h)
+{
+    return is_single(h) && columns_fit(h->lat, h->dtype, h->dims[0], h->dims[1], h->dims[2]);
+}
 // The tile kernel has a plan for this box.
 bool tile_ok(const lbm_ctx* h) { return is_single(h) && h->tile.steps > 0; }
 
 // Without a choice by the caller or the tuner: the tile kernel where it has a
-// plan; the two-step kernel in FP32 and FP64 from two column-planes per compute
-// unit on (D3Q19 FP32, us per step, one-site against two-step: 64^3 8.5 / 7.3,
-// 128^3 53.2 / 36.6, 256^3 422 / 247; 16-bit storage at 128^3 26 / 32); else the
-// one-site step, also where the caller set a launch shape, which is that
-// step's.
+// plan; in FP32 and FP64 the two-step kernel on larger boxes; else the one-site
+// step, also where the caller set a launch shape, which is that step's.
+// Two-step against one-site, us per step of D3Q19 FP32: tiles of 64 columns 64^3
+// 7.3 / 8.5, 128^3 36 / 53, 256^3 248 / 422; other tiles 65^3 12.0 / 12.0,
+// 33 x 150 x 90 14-16 / 16.8, 100^3 17.4 / 35, 201 x 150 x 77 54 / 76, 255^3 363 /
+// 646, FP64 100^3 38 / 59.  In 16-bit storage the one-site step is faster on
+// aligned rows (128^3 26 / 32) and little slower on others (100^3 22.5 / 18).
 int auto_kernel(const lbm_ctx* h)
 {
     if (h->block > 0 || h->grid > 0) return LBM_KERNEL_SCALAR;
     if (tile_ok(h)) return LBM_KERNEL_TILE;
-    if (h->elem >= 4 && two_step_ok(h) &&
-        h->nsites / (kTwoStepTileX * two_step_tile_y(h->elem)) >= 2 * int64_t(h->cus))
-        return LBM_KERNEL_TWO_STEP;
+    if (h->elem >= 4) {
+        if (two_step_ok(h) && h->nsites >= kTwoStepSites) return LBM_KERNEL_TWO_STEP;
+        if (columns_ok(h) && h->nsites >= kColumnsSites) return LBM_KERNEL_COLUMNS;
+    }
     return LBM_KERNEL_SCALAR;
 }
 
@@ -452,7 +474,12 @@ bool twisted(const lbm_ctx* h) { return is_single(h) && effective_kernel(h) == L
 bool one_buffer(const lbm_ctx* h) { return in_place(h) || twisted(h); }
 
 // The two-step / tile kernel is the one in use.
-bool two_step(const lbm_ctx* h) { return is_single(h) && effective_kernel(h) == LBM_KERNEL_TWO_STEP; }
+bool two_step(const lbm_ctx* h)
+{
+    if (!is_single(h)) return false;
+    const int k = effective_kernel(h);
+    return k == LBM_KERNEL_TWO_STEP || k == LBM_KERNEL_COLUMNS;
+}
 
 bool tiled(const lbm_ctx* h) { return is_single(h) && effective_kernel(h) == LBM_KERNEL_TILE; }
 
@@ -534,12 +561,14 @@ hipError_t launch_two(lbm_ctx* h, int parity, hipStream_t s)
     geo.nx = int(h->dims[0]);
     geo.ny = int(h->dims[1]);
     geo.nz = int(h->dims[2]);
-    geo.ncx = int(h->dims[0] / kTwoStepTileX);
-    const long long ncy = h->dims[1] / two_step_tile_y(h->elem);
+    column_tile(h->elem, h->dims[0], h->dims[1], &geo.tx, &geo.ty);
+    geo.ncx = int((h->dims[0] + geo.tx - 1) / geo.tx);
+    const long long ncy = (h->dims[1] + geo.ty - 1) / geo.ty;
     geo.total = (long long)geo.ncx * ncy * geo.nz;
     const int grid = two_step_grid(h);
     geo.per = (geo.total + grid - 1) / grid;
     geo.xcd_order = (grid % 8 == 0) ? 1 : 0;
+    geo.cached_stores = h->state_bytes >= kCachedStoresFrom && h->state_bytes <= kCachedStoresTo;
     return launch_step2(h->lattice, h->dtype, h->K, step_kind(h), h->buf[parity], h->buf[parity ^ 1], geo,
                         1.0 - 1.0 / h->tau[0], h->theta, grid, s);
 }
@@ -855,13 +884,16 @@ lbm_status lbm_set_kernel(lbm_t h, int32_t kernel)
         if (lbm_status st = check_handle(h)) return st;
         if (kernel != LBM_KERNEL_AUTO && kernel != LBM_KERNEL_SCALAR && kernel != LBM_KERNEL_ROW_WAVE &&
             kernel != LBM_KERNEL_IN_PLACE && kernel != LBM_KERNEL_TWO_ROW && kernel != LBM_KERNEL_TWIST &&
-            kernel != LBM_KERNEL_TWO_STEP && kernel != LBM_KERNEL_TILE)
+            kernel != LBM_KERNEL_TWO_STEP && kernel != LBM_KERNEL_TILE && kernel != LBM_KERNEL_COLUMNS)
             return fail(LBM_EINVAL, "unknown kernel variant %d", kernel);
         if (kernel == LBM_KERNEL_TWO_STEP && !two_step_ok(h))
             return fail(LBM_EINVAL,
                         "the two-step kernel needs a single D3Q15 or D3Q19 box with nx a multiple of %d, ny a "
                         "multiple of %d and one z-plane of populations below 2 GiB",
                         kTwoStepTileX, two_step_tile_y(h->elem));
+        if (kernel == LBM_KERNEL_COLUMNS && !columns_ok(h))
+            return fail(LBM_EINVAL, "the two-step kernel on columns needs a single D3Q15 or D3Q19 box and one z-plane "
+                                    "of populations below 2 GiB");
         if (kernel == LBM_KERNEL_TILE && !tile_ok(h))
             return fail(LBM_EINVAL, "the tile kernel needs a single D2Q9, D3Q15 or D3Q19 box for which it has a plan");
         if ((kernel == LBM_KERNEL_IN_PLACE || kernel == LBM_KERNEL_TWIST) && !is_single(h))
@@ -1016,7 +1048,8 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
         LaunchChoice best;
         if (tune_cache_lookup(cache_path, key, &best)) {
             // the cache is a text file: take only values this library can launch
-            if (best.kernel < LBM_KERNEL_AUTO || best.kernel > LBM_KERNEL_TILE) best.kernel = LBM_KERNEL_SCALAR;
+            if (best.kernel < LBM_KERNEL_AUTO || best.kernel > LBM_KERNEL_COLUMNS) best.kernel = LBM_KERNEL_SCALAR;
+            if (best.kernel == LBM_KERNEL_COLUMNS && !columns_ok(h)) best.kernel = LBM_KERNEL_SCALAR;
             if (best.kernel == LBM_KERNEL_TILE && !tile_ok(h)) best.kernel = LBM_KERNEL_SCALAR;
             if (best.kernel == LBM_KERNEL_TWO_STEP && !two_step_ok(h)) best.kernel = LBM_KERNEL_SCALAR;
             if (!(best.block == 0 || (best.block >= 64 && best.block <= 256 && best.block % 64 == 0))) best.block = 0;
@@ -1044,14 +1077,19 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
                 cand.push_back({LBM_KERNEL_IN_PLACE, int(row), 0});
                 cand.push_back({LBM_KERNEL_TWIST, int(row), 0});
             }
-            if (h->dims[1] % 2 == 0) cand.push_back({LBM_KERNEL_TWO_ROW, 256, 0});
-            if (row_wave_sites(h)) cand.push_back({LBM_KERNEL_ROW_WAVE, 0, 0});
-            // the two-step kernel at one and two blocks per compute unit
-            if (two_step_ok(h)) {
-                cand.push_back({LBM_KERNEL_TWO_STEP, 0, 0});
-                cand.push_back({LBM_KERNEL_TWO_STEP, 0, 2 * h->cus});
+            if (tile_ok(h)) {
+                cand.push_back({LBM_KERNEL_TILE, 0, 0});
+            } else if (columns_ok(h)) {
+                // the two-step kernel at one and two blocks per compute unit
+                const int k = two_step_ok(h) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_COLUMNS;
+                cand.push_back({k, 0, 0});
+                cand.push_back({k, 0, 2 * h->cus});
+            } else {
+                // one-step forms that were never the fastest where one of the
+                // above runs
+                if (h->dims[1] % 2 == 0) cand.push_back({LBM_KERNEL_TWO_ROW, 256, 0});
+                if (row_wave_sites(h)) cand.push_back({LBM_KERNEL_ROW_WAVE, 0, 0});
             }
-            if (tile_ok(h)) cand.push_back({LBM_KERNEL_TILE, 0, 0});
         } else {
             for (int b : {64, 128, 256})
                 for (int g : {0, 1024, 2048, 4096}) cand.push_back({LBM_KERNEL_SCALAR, b, g});

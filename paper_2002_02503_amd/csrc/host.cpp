@@ -6,7 +6,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <cstdlib>
 #include <fstream>
 #include <sstream>
 
@@ -101,14 +100,32 @@ bool check_boxes(const LatticeInfo& L, int dtype, int nbox, const int64_t* dims,
     return true;
 }
 
-bool two_step_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz)
+bool columns_fit(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz)
 {
     const size_t elem = storage_bytes(dtype);
     if (L.D != 3 || L.R != 1 || elem == 0) return false;
     if (nx < 1 || ny < 1 || nz < 1 || nx > INT32_MAX || ny > INT32_MAX || nz > INT32_MAX) return false;
-    if (nx % kTwoStepTileX != 0 || ny % two_step_tile_y(elem) != 0) return false;
     const uint64_t plane_sites = uint64_t(nx) * uint64_t(ny);  // below 2^62
     return plane_sites <= ((uint64_t(1) << 31) - 1) / (uint64_t(L.Q) * elem);
+}
+
+bool two_step_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz)
+{
+    return columns_fit(L, dtype, nx, ny, nz) && nx % kTwoStepTileX == 0 &&
+           ny % two_step_tile_y(storage_bytes(dtype)) == 0;
+}
+
+// n cut into pieces of at most `most`, of nearly equal size.
+static int even_piece(int64_t n, int64_t most)
+{
+    const int64_t pieces = (n + most - 1) / most;
+    return int((n + pieces - 1) / pieces);
+}
+
+void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
+{
+    *tx = (nx % kTwoStepTileX == 0) ? kTwoStepTileX : even_piece(nx, 128);
+    *ty = even_piece(ny, two_step_threads(elem) / (*tx + 2) - 2);
 }
 
 int64_t tile_region(const LatticeInfo& L, const TilePlan& p, int64_t nx, int steps)
@@ -133,13 +150,6 @@ bool tile_plan_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int
     const int64_t limit = int64_t(1) << 32;
     if (nx > limit / (L.Q * elem) / ny / nz) return false;
     return true;
-}
-
-// n cut into pieces of at most `most`, of nearly equal size.
-static int even_piece(int64_t n, int64_t most)
-{
-    const int64_t pieces = (n + most - 1) / most;
-    return int((n + pieces - 1) / pieces);
 }
 
 bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, int cus, TilePlan* out)

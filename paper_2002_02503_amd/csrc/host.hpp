@@ -50,12 +50,32 @@ constexpr int kBlockSites = 64;                  // sites per block of a batched
 constexpr int kTwoStepTileX = 64;
 constexpr int two_step_tile_y(size_t elem) { return elem == 8 ? 4 : 8; }
 
+// Threads of its blocks: whole waves for the tile and its ring.
+constexpr int two_step_threads(size_t elem)
+{
+    return ((kTwoStepTileX + 2) * (two_step_tile_y(elem) + 2) + 63) / 64 * 64;
+}
+
 // Whether the two-step kernel applies to a single nx x ny x nz box: a 3-D
 // lattice whose velocity components are at most 1 in magnitude (a one-site
 // ring), nx and ny multiples of the tile, and one z-plane of populations
 // (Q nx ny values) below 2 GiB, since offsets inside a plane are formed in
 // 32 bits.
 bool two_step_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz);
+
+// The same kernel on columns of any size ("columns"): the lattice and the plane
+// limit alone.
+bool columns_fit(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz);
+
+// Column tile of the two-step kernel for a box: 64 x two_step_tile_y where nx
+// is a multiple of 64; else x in even pieces of at most 128, since rows that
+// do not start on a cache line pay for partly used lines at both ends of a
+// piece, and as many rows as the block's threads hold.  Measured, us per step
+// (tile): D3Q19 FP32 201 x 150 x 77 54 (101 x 4), 62 (67 x 8), 71 (51 x 11);
+// 100^3 21 (100 x 4), 29 (50 x 10), 33 (34 x 17); 255^3 363 (128 x 3), 411 (64 x
+// 8); 160^3 83 (80 x 6 and 160 x 2), 93 (32 x 18); FP64 100^3 38 (100 x 2), 44
+// (50 x 6).
+void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 
 constexpr int kTileMaxSteps = 16;
 constexpr int64_t kTileMaxLds = 160 * 1024;  // a compute unit's LDS

@@ -29,15 +29,18 @@ struct StepGeom {
 };
 
 // Single box, two-step kernel (step2.hpp): the (x, y) plane is cut into
-// columns of the output tile, ncx of them along x; column-plane
+// columns of tx x ty sites (the last ones of a row or column of them may be
+// narrower), ncx of them along x; column-plane
 // w = column * nz + z, and block b takes the `per` consecutive column-planes
 // from (b or its XCD-ordered index) * per on, `total` of them in all.
 struct Step2Geom {
     int nx, ny, nz;
     int ncx;
+    int tx, ty;
     long long total;
     long long per;
     int xcd_order;        // 1: consecutive columns on one XCD (grid a multiple of 8)
+    int cached_stores;    // 1: stores with the default cache policy, else non-temporal
 };
 
 // Single box, several steps per launch in LDS (step_tile.hpp): tiles of tx x ty

@@ -10,21 +10,22 @@
 namespace lbm {
 
 // ---------------------------------------------------------------------------
-// A block owns a column of TX x TY sites of the (x, y) plane over a range of
-// z-planes and walks it upwards in z.  At each plane p it
-//   1. takes the step t -> t + 1 at the (TX + 2) x (TY + 2) sites of the
+// A block owns a column of tx x ty sites of the (x, y) plane (host.hpp,
+// column_tile) over a range of z-planes and walks it upwards in z.  At each
+// plane p it
+//   1. takes the step t -> t + 1 at the (tx + 2) x (ty + 2) sites of the
 //      column and its one-site ring, one site per thread, pulling from HBM,
 //      and writes every result into an LDS plane in the storage type (so a
 //      read gives back exactly what a store to HBM and a reload would);
-//   2. takes the step t + 1 -> t + 2 at the TX x TY column sites of plane
+//   2. takes the step t + 1 -> t + 2 at the tx x ty column sites of plane
 //      p - 1.  Its pulls from plane p - 1 + c_z come from the LDS plane just
 //      written (c_z = -1) or from registers holding LDS values read one plane
 //      (c_z = 0) or two planes (c_z = +1) earlier; thread j owns the column
-//      site (j % TX, j / TX) for the whole walk, so step 2 runs on
-//      TX TY / 64 whole waves.
+//      site (j % tx, j / tx) for the whole walk, so step 2 runs on whole
+//      waves but the last.
 // The state at t + 1 never reaches HBM: one launch reads and writes the state
 // once per two steps.  The price is the ring, computed in step 1 only, which
-// adds (TX + 2)(TY + 2) / (TX TY) - 1 of one step's arithmetic, and two extra
+// adds (tx + 2)(ty + 2) / (tx ty) - 1 of one step's arithmetic, and two extra
 // step-1 planes per column segment.  Each site's arithmetic is k_step's on
 // the same values, so the launch gives the bits of two k_step launches.
 // The LDS planes are double-buffered: a wave that has finished step 2 at
@@ -41,7 +42,12 @@ namespace lbm {
 // the traffic.  Measured on D3Q19 256^3, us per step, non-temporal against
 // cached c_x = 0 loads: FP32 317 against 249, FP64 562 against 477, FP16 254
 // against 231; 128^3 FP32 39.5 against 36.6.  The stores are read by no one
-// in this launch and stay non-temporal (cached: 258 FP32, 495 FP64).
+// in this launch and are non-temporal (cached: 258 FP32, 495 FP64) but where
+// the state is small enough for the Infinity Cache and large enough not to
+// end as dirty lines in the L2s (api.hip, kCachedStoresFrom).
+// The tile's sides are run-time values; as compile-time constants (64 x 8, the
+// only tile then) the kernel ran no faster: 248 against 248 us per FP32 step of
+// D3Q19 256^3, 484 against 476 in FP64, 36.0 against 36.3 at 128^3.
 // Blocks are dealt to the eight XCDs in turn; with the grid a multiple of 8
 // the block -> column order puts consecutive columns (which share ring rows)
 // on one XCD and its L2 (measured on D3Q19 256^3 FP32: 2% faster than the
@@ -51,10 +57,10 @@ namespace lbm {
 template <class S>
 constexpr int step2_threads()
 {
-    return (kTwoStepTileX + 2) * (two_step_tile_y(sizeof(S)) + 2);
+    return two_step_threads(sizeof(S));
 }
 
-template <class L, class S, int K, int KIND>
+template <class L, class S, int K, int KIND, bool CACHED_STORES>
 __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __restrict__ src, S* __restrict__ dst,
                                                                  Step2Geom geo, typename Store<S>::R omega,
                                                                  typename Store<S>::R theta)
@@ -63,10 +69,9 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
     using R = typename ST::R;
     constexpr bool PROJ = !std::is_same<R, double>::value;
     constexpr int Q = L::Q;
-    constexpr int TX = kTwoStepTileX, TY = two_step_tile_y(sizeof(S));
-    constexpr int WX = TX + 2, NT = WX * (TY + 2);
+    constexpr int NT = step2_threads<S>();
     static_assert(L::D == 3 && L::R == 1, "a one-site ring in x, y and z");
-    static_assert((TX * TY) % 64 == 0, "step 2 on whole waves");
+    const int tx = geo.tx, ty = geo.ty, wx = tx + 2;
     // How an element's address is formed.  SCALAR_BASE: a uniform row pointer
     // (z-plane, tile row m; scalar registers) plus the lane's 32-bit offset in
     // the plane, so no 64-bit vector address is held.  Otherwise the lane's
@@ -79,10 +84,11 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
     __shared__ S lplane[2][Q][NT];
 
     const int tid = threadIdx.x;
-    const int hx = tid % WX, hy = tid / WX;  // step-1 site in the ring-extended column
-    const bool owner = tid < TX * TY;
-    const int ox = tid % TX, oy = tid / TX;  // step-2 site (owners)
-    const int oh = (oy + 1) * WX + ox + 1;   // the same, ring-extended
+    const int hy = tid / wx, hx = tid - hy * wx;  // step-1 site in the ring-extended column
+    const bool owner = tid < tx * ty;
+    const int oy = tid / tx, ox = tid - oy * tx;  // step-2 site (owners)
+    const int oh = owner ? (oy + 1) * wx + ox + 1 : wx + 1;   // the same, ring-extended
+    const int ohy[3] = {oh - wx, oh, oh + wx};
     const unsigned row_bytes = unsigned(geo.nx) * unsigned(sizeof(S));
     const unsigned tile_bytes = unsigned(Q) * row_bytes;  // one x-row's tile
     const long long plane_bytes = (long long)tile_bytes * geo.ny;
@@ -98,8 +104,11 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
         const int za = int(w - col * geo.nz);
         const int zb = za + int(seg_end - w);
         w = seg_end;
-        const int x0 = int(col % geo.ncx) * TX, y0 = int(col / geo.ncx) * TY;
-        const int x = wrap_coord(x0 + hx - 1, geo.nx), y = wrap_coord(y0 + hy - 1, geo.ny);
+        const int x0 = int(col % geo.ncx) * tx, y0 = int(col / geo.ncx) * ty;
+        // lanes past the ring (and the ring of a narrower last column) repeat
+        // sites of the box
+        const int x = wrap_coord(x0 + hx - 1, geo.nx), y = wrap_coord(y0 + min(hy, ty + 1) - 1, geo.ny);
+        const bool writer = owner && x0 + ox < geo.nx && y0 + oy < geo.ny;
         // Byte offsets inside a z-plane of the step-1 site's x- and
         // y-neighbours, fixed for the whole column.
         unsigned xoff[3], yoff[3];
@@ -151,7 +160,7 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
                 unroll<Q>([&](auto I) {
                     constexpr int i = decltype(I)::value;
                     constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-                    const R v = ST::get(&buf[i][oh - cx - cy * WX]);
+                    const R v = ST::get(&buf[i][0] + (ohy[1 - cy] - cx));
                     if constexpr (cz == -1) {
                         h[i] = v;
                     } else if constexpr (cz == 0) {
@@ -166,16 +175,18 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
                 if (k >= 2) {  // plane p - 1 has all its inputs
                     collide_site<L, K, KIND, PROJ, R>(h, omega, theta);
                     char* out = reinterpret_cast<char*>(dst) + (long long)wrap_coord(p - 1, geo.nz) * plane_bytes;
-                    unroll<Q>([&](auto M) {
-                        constexpr int m = decltype(M)::value;
-                        constexpr int i = mem_pop<L>(m);
-                        char* p8;
-                        if constexpr (SCALAR_BASE)
-                            p8 = (out + (long long)m * row_bytes) + own;
-                        else
-                            p8 = out + (own + unsigned(m) * row_bytes);
-                        ST::put_nt(reinterpret_cast<S*>(p8), h[i]);
-                    });
+                    if (writer)
+                        unroll<Q>([&](auto M) {
+                            constexpr int m = decltype(M)::value;
+                            constexpr int i = mem_pop<L>(m);
+                            char* p8;
+                            if constexpr (SCALAR_BASE)
+                                p8 = (out + (long long)m * row_bytes) + own;
+                            else
+                                p8 = out + (own + unsigned(m) * row_bytes);
+                            if constexpr (CACHED_STORES) ST::put(reinterpret_cast<S*>(p8), h[i]);
+                            else ST::put_nt(reinterpret_cast<S*>(p8), h[i]);
+                        });
                 }
             }
         }
@@ -192,8 +203,12 @@ hipError_t launch_step2_l(int K, int kind, const void* src, void* dst, const Ste
             using R = typename Store<S>::R;
             constexpr int KK = decltype(Kc)::value;
             constexpr int KD = decltype(Kind)::value;
-            k_step2<L, S, KK, KD><<<dim3(unsigned(grid)), step2_threads<S>(), 0, s>>>(
-                static_cast<const S*>(src), static_cast<S*>(dst), geo, R(omega), R(theta));
+            if (geo.cached_stores)
+                k_step2<L, S, KK, KD, true><<<dim3(unsigned(grid)), step2_threads<S>(), 0, s>>>(
+                    static_cast<const S*>(src), static_cast<S*>(dst), geo, R(omega), R(theta));
+            else
+                k_step2<L, S, KK, KD, false><<<dim3(unsigned(grid)), step2_threads<S>(), 0, s>>>(
+                    static_cast<const S*>(src), static_cast<S*>(dst), geo, R(omega), R(theta));
             return hipGetLastError();
         });
     } else {

@@ -19,7 +19,7 @@ LIB_PATH = os.path.join(_HERE, "liblbm.so")
 LATTICES = {"D2Q9": 0, "D3Q19": 1, "D3Q39": 2, "D3Q15": 3}
 DTYPES = {"fp64": 0, "fp32": 1, "fp16": 2, "bf16": 3}
 DTYPE_BYTES = {"fp64": 8, "fp32": 4, "fp16": 2, "bf16": 2}
-KERNELS = {"auto": 0, "scalar": 1, "row_wave": 2, "in_place": 3, "two_row": 4, "twist": 5, "two_step": 6, "tile": 7}
+KERNELS = {"auto": 0, "scalar": 1, "row_wave": 2, "in_place": 3, "two_row": 4, "twist": 5, "two_step": 6, "tile": 7, "columns": 8}
 COLLISIONS = {"filtered": 0, "bgk": 1}
 STATUS = {0: "LBM_OK", -1: "LBM_EINVAL", -2: "LBM_ENOMEM", -3: "LBM_EDEVICE", -4: "LBM_ENODEV",
           -5: "LBM_ESTATE", -6: "LBM_ENUMERIC"}
@@ -185,8 +185,8 @@ class Simulation:
     weight theta (lbm_set_collision), launch shape (block, grid) and steps per
     captured graph.  kernel picks the single-box step (lbm_set_kernel; a key of
     KERNELS: "scalar", "row_wave", "in_place", "two_row", "twist",
-    "two_step" or "tile", the last two taking two or more steps per launch);
-    "auto" leaves the
+    "two_step", "columns" or "tile", the last three taking two or more steps
+    per launch); "auto" leaves the
     choice to the library, and tune() to measurement.
     """
 

@@ -1,0 +1,64 @@
+"""The two-step kernel on columns of any size against the one-site step: the
+same bits for pieces of rows with a narrower last one, sides of one to three
+sites, narrow last rows of columns, states on both sides of its store policy,
+every storage type and collision kind; and the library's choice of it."""
+import numpy as np
+import pytest
+
+from gpu_common import run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _fields(dims, seed):
+    rng = np.random.default_rng(seed)
+    nx, ny, nz = dims
+    return 1.0 + rng.uniform(-0.01, 0.01, size=(nz, ny, nx)), rng.uniform(-0.05, 0.05, size=(3, nz, ny, nx))
+
+
+CASES = [
+    ("D3Q19", (201, 15, 7), "fp32", {"theta": 0.5}),   # rows of 101 and 100
+    ("D3Q19", (129, 9, 5), "fp64", {}),                # 65 and 64
+    ("D3Q19", (257, 23, 3), "fp16", {}),               # 86, 86, 85
+    ("D3Q19", (1, 1, 1), "fp32", {}),
+    ("D3Q19", (2, 3, 1), "fp64", {"theta": 0.5}),
+    ("D3Q19", (3, 2, 2), "bf16", {}),
+    ("D3Q19", (8, 169, 12), "fp32", {"K": 2}),         # 57 rows a column, the last 55
+    ("D3Q19", (64, 8, 4), "fp32", {}),                 # the aligned tile
+    ("D3Q19", (96, 6, 5), "fp32", {"collision": "bgk"}),
+    ("D3Q15", (100, 41, 9), "fp64", {}),
+    ("D3Q15", (33, 50, 6), "fp32", {"theta": 0.3}),
+    ("D3Q19", (100, 100, 60), "fp32", {}),             # 46 MB: cached stores
+]
+
+
+@pytest.mark.parametrize("lattice,dims,dtype,kw", CASES)
+@pytest.mark.parametrize("steps", [1, 2, 15])
+def test_columns_equal_one_site_step(lattice, dims, dtype, kw, steps):
+    rho, u = _fields(dims, seed=steps + sum(dims))
+    a = run_gpu(lattice, dims, 0.6, dtype, rho, u, steps, kernel="columns", **kw)
+    b = run_gpu(lattice, dims, 0.6, dtype, rho, u, steps, kernel="scalar", **kw)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("grid", [1, 5, 16, 999])
+def test_columns_any_grid(grid):
+    dims = (70, 31, 9)
+    rho, u = _fields(dims, seed=grid)
+    a = run_gpu("D3Q19", dims, 0.57, "fp32", rho, u, 14, kernel="columns", grid=grid)
+    b = run_gpu("D3Q19", dims, 0.57, "fp32", rho, u, 14, kernel="scalar")
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+def test_columns_refusals_and_the_default_choice():
+    from paper_2002_02503_amd import lbm
+
+    for lattice, dims in [("D2Q9", (64, 64, 1)), ("D3Q39", (64, 32, 4))]:
+        with pytest.raises(lbm.LBMError) as e:
+            lbm.Simulation(lattice, dims, 0.6, kernel="columns", torch_memory=False)
+        assert e.value.name == "LBM_EINVAL"
+    names = {v: k for k, v in lbm.KERNELS.items()}
+    for dims, dtype, want in [((201, 150, 77), "fp32", "columns"), ((100, 100, 100), "fp64", "columns"),
+                              ((100, 100, 100), "bf16", "scalar"), ((65, 65, 65), "fp32", "scalar")]:
+        with lbm.Simulation("D3Q19", dims, 0.8, dtype=dtype, torch_memory=False) as sim:
+            assert names[sim.info()["kernel"]] == want, (dims, dtype)
