@@ -69,9 +69,10 @@ typedef enum {
 
 /* Step-kernel variants for a single box (lbm_set_kernel). */
 typedef enum {
-    LBM_KERNEL_AUTO = 0,      /* until a tuned choice is set: the tile kernel where it applies, in FP32 and FP64
-                                 the two-step kernel (on columns of any size where nx and ny do not fit it)
-                                 where the box is large enough to gain (64^3; 400,000 sites), else the scalar step, also where a launch shape was set */
+    LBM_KERNEL_AUTO = 0,      /* until a tuned choice is set: the tile kernel where it applies, the two-step
+                                 kernel (on columns of any size where nx and ny do not fit it) where the box
+                                 is large enough to gain, else the scalar step, also where a launch shape
+                                 was set */
     LBM_KERNEL_SCALAR = 1,    /* one site per thread, 4/8-byte accesses */
     LBM_KERNEL_ROW_WAVE = 2,  /* V sites per lane, 8/16-byte accesses, x-neighbours by lane shuffle */
     LBM_KERNEL_IN_PLACE = 3,  /* one site per thread on one buffer: each step reads and writes the same

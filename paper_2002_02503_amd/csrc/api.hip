@@ -176,21 +176,21 @@ bool columns_ok(const lbm_ctx* h)
 bool tile_ok(const lbm_ctx* h) { return is_single(h) && h->tile.steps > 0; }
 
 // Without a choice by the caller or the tuner: the tile kernel where it has a
-// plan; in FP32 and FP64 the two-step kernel on larger boxes; else the one-site
-// step, also where the caller set a launch shape, which is that step's.
+// plan; the two-step kernel on larger boxes (in 16-bit storage only where rows
+// are not whole cache lines); else the one-site step, also where the caller set a launch shape, which is that step's.
 // Two-step against one-site, us per step of D3Q19 FP32: tiles of 64 columns 64^3
 // 7.3 / 8.5, 128^3 36 / 53, 256^3 248 / 422; other tiles 65^3 12.0 / 12.0,
 // 33 x 150 x 90 14-16 / 16.8, 100^3 17.4 / 35, 201 x 150 x 77 54 / 76, 255^3 363 /
-// 646, FP64 100^3 38 / 59.  In 16-bit storage the one-site step is faster on
-// aligned rows (128^3 26 / 32) and little slower on others (100^3 22.5 / 18).
+// 646, FP64 100^3 38 / 59, FP16 100^3 18.4 / 22.5.  In 16-bit storage on rows of
+// 64 columns both are bound by instruction issue and nothing is gained (FP16
+// 128^3 26.4 / 26, 256^3 209 / 206).
 int auto_kernel(const lbm_ctx* h)
 {
     if (h->block > 0 || h->grid > 0) return LBM_KERNEL_SCALAR;
     if (tile_ok(h)) return LBM_KERNEL_TILE;
-    if (h->elem >= 4) {
-        if (two_step_ok(h) && h->nsites >= kTwoStepSites) return LBM_KERNEL_TWO_STEP;
-        if (columns_ok(h) && h->nsites >= kColumnsSites) return LBM_KERNEL_COLUMNS;
-    }
+    if (two_step_ok(h))
+        return (h->elem >= 4 && h->nsites >= kTwoStepSites) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_SCALAR;
+    if (columns_ok(h) && h->nsites >= kColumnsSites) return LBM_KERNEL_COLUMNS;
     return LBM_KERNEL_SCALAR;
 }
 

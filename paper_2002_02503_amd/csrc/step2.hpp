@@ -33,8 +33,8 @@ namespace lbm {
 // plane p + 1 while slower waves still read, so one barrier per plane
 // suffices (the barrier after plane p + 1's writes comes after every read of
 // plane p - 1's buffer, which plane p + 2 refills).
-// The loads of plane p + 1 are issued before plane p's collisions, so they
-// are in flight during both steps.
+// The loads of plane p + 1 are issued during plane p (LATE_LOADS below), so they
+// are in flight while it collides.
 // Every load keeps the default cache policy.  A ring row belongs to up to
 // three columns, whose blocks share an L2 and read it at about the same time;
 // with the c_x = 0 populations loaded non-temporally, as the one-site step
@@ -81,6 +81,13 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
     // first: its 20-60 fewer registers per lane keep it from spilling (330
     // against 400 us per FP32 step).
     constexpr bool SCALAR_BASE = sizeof(S) == 8 || KIND == kFilteredQ;
+    // When the next plane's loads are issued: before this plane's step 1 into
+    // registers of their own, or after it into its own (LATE_LOADS), which saves
+    // Q moves a plane and Q registers but leaves only step 2 to hide the
+    // latency.  Measured on D3Q19 256^3, us per step, early against late: FP64
+    // 490 / 474, FP16 220 / 209, FP32 248 / 260, BF16 222 / 231, energy flux 287 /
+    // 286.
+    constexpr bool LATE_LOADS = std::is_same<S, double>::value || std::is_same<S, _Float16>::value;
     __shared__ S lplane[2][Q][NT];
 
     const int tid = threadIdx.x;
@@ -140,20 +147,25 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
 
         // held LDS values: read from the first plane on, used from the third
         // (k >= 2); zeroed so that no read is of an indeterminate value
-        R next[Q], hold0[Q] = {}, hold1a[Q] = {}, hold1b[Q] = {};
+        R g[Q], hold0[Q] = {}, hold1a[Q] = {}, hold1b[Q] = {};
+        [[maybe_unused]] R next[Q];
         const int planes = zb - za + 2;  // step-1 planes za - 1 .. zb
-        pull(za - 1, next);
+        if constexpr (LATE_LOADS) pull(za - 1, g);
+        else pull(za - 1, next);
         for (int k = 0; k < planes; ++k) {
             const int p = za - 1 + k;
-            R g[Q];
-            unroll<Q>([&](auto I) { g[decltype(I)::value] = next[decltype(I)::value]; });
-            if (k + 1 < planes) pull(p + 1, next);
+            if constexpr (!LATE_LOADS) {
+                unroll<Q>([&](auto I) { g[decltype(I)::value] = next[decltype(I)::value]; });
+                if (k + 1 < planes) pull(p + 1, next);
+            }
             collide_site<L, K, KIND, PROJ, R>(g, omega, theta);
             S(&buf)[Q][NT] = lplane[k & 1];
             unroll<Q>([&](auto I) {
                 constexpr int i = decltype(I)::value;
                 ST::put(&buf[i][tid], g[i]);
             });
+            if constexpr (LATE_LOADS)
+                if (k + 1 < planes) pull(p + 1, g);
             __syncthreads();
             if (owner) {
                 R h[Q];
