@@ -213,8 +213,9 @@ lbm_status lbm_set_launch(lbm_t h, int32_t block, int32_t grid);
  * moments, totals and residual read it as it is, and lbm_get_state returns the
  * natural layout (rearranged on the host).  Switching kernels later (lbm_tune)
  * allocates the second buffer.  Batches always use the batched kernel (one
- * wave per 64-site block); for them LBM_KERNEL_AUTO and LBM_KERNEL_SCALAR are
- * accepted and the other variants are LBM_EINVAL.
+ * wave per 64-site block) or, two steps per launch, LBM_KERNEL_COLUMNS, which
+ * LBM_KERNEL_AUTO takes for large FP32 and FP64 batches; for them the other
+ * variants but LBM_KERNEL_SCALAR are LBM_EINVAL.
  * LBM_KERNEL_TWIST (single box) also steps inside one buffer.  The state is
  * kept in twisted layouts: population i of site x sits at site x + b_i, b_i
  * the positive part of c_i component by component, in tile row m(i) after an
@@ -226,8 +227,8 @@ lbm_status lbm_set_launch(lbm_t h, int32_t block, int32_t grid);
  * 64, ny a multiple of 8 (4 for FP64 storage) and one z-plane of populations
  * (Q nx ny values) below 2 GiB, else LBM_EINVAL.  An odd step count ends with
  * one step of the scalar kernel; the state stays in the natural layout.
- * LBM_KERNEL_COLUMNS needs a single D3Q15 or D3Q19 box with one z-plane of
- * populations below 2 GiB, else LBM_EINVAL.
+ * LBM_KERNEL_COLUMNS needs D3Q15 or D3Q19 and, for every box, one z-plane of
+ * populations below 2 GiB, else LBM_EINVAL.  It also steps batches.
  * LBM_KERNEL_TILE needs a single D2Q9, D3Q15 or D3Q19 box whose state is below
  * 4 GiB (D2Q9 of any other size; in 3-D at most 160 sites per compute unit),
  * else LBM_EINVAL.  The library chooses the tile and the steps per launch; the
@@ -244,11 +245,10 @@ lbm_status lbm_set_kernel(lbm_t h, int32_t kernel);
  * round.  Single box: the scalar step at 64/128/256 threads per block, the
  * in-place and twist steps at 256, all three at one whole x-row per block when
  * nx rounds up to 192 lanes, and either the tile kernel, or the two-step kernel
- * (on columns of any size where nx and ny do not fit it) at one and at two
- * blocks per compute unit, or, where neither applies, the two-row (ny even) and
- * row-wave steps.  Batch: 64/128/256 threads per block, with
- * one wave per 64-site block of the layout or 1024/2048/4096 persistent
- * blocks.  The state is saved before and restored after, so t and the
+ * (on columns of any size where nx and ny do not fit it), or, where neither
+ * applies, the two-row (ny even) and row-wave steps.  Batch: 64/128/256 threads
+ * per block with one wave per 64-site block of the layout, and
+ * LBM_KERNEL_COLUMNS where it applies.  The state is saved before and restored after, so t and the
  * populations are unchanged (all candidates compute the same bits).  Choices are appended to the text file `cache_path` (NULL: the
  * path in the environment variable LBM_TUNE_CACHE, or no cache); a later call
  * with the same lattice, dtype, K, collision kind and geometry reuses the

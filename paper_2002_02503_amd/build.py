@@ -29,12 +29,12 @@ STORAGE = ["double", "float", "_Float16", "bf16_t"]
 # units compile in parallel in similar times.
 INSTANCE_GROUPS = ([("D2Q9", STORAGE), ("D3Q15", STORAGE), ("D3Q19", STORAGE)]
                    + [("D3Q39", [s]) for s in STORAGE])
-# Two-step kernel instances (lattices with a one-site ring), one unit per
-# (lattice, storage type): each instance holds two collisions.
+# Two-step kernel instances, single box and batch (3-D lattices with a one-site
+# ring), one unit per (lattice, storage type): each instance holds two collisions.
+STEP2_GROUPS = [(lat, [s]) for lat in ("D3Q15", "D3Q19") for s in STORAGE]
 # Tile kernel instances (several steps per launch in LDS), one unit per
 # (lattice, storage type).
 TILE_GROUPS = [(lat, [s]) for lat in ("D2Q9", "D3Q15", "D3Q19") for s in STORAGE]
-STEP2_GROUPS = [(lat, [s]) for lat in ("D3Q15", "D3Q19") for s in STORAGE]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -57,13 +57,14 @@ def _compile(src: str, obj: str) -> None:
 
 def _instance_units(gendir: str) -> list:
     """Write the step-kernel instance units: each includes step.hpp (single
-    box), step_batch.hpp (batch), step2.hpp (two steps per launch) or
-    step_tile.hpp (several steps per launch) and instantiates the launchers of one group of (lattice, storage type)
+    box), step_batch.hpp (batch), step2.hpp or step2_batch.hpp (two steps per
+    launch) or step_tile.hpp (several steps per launch) and instantiates the launchers of one group of (lattice, storage type)
     pairs."""
     units = []
     families = [("step", "step.hpp", "LBM_DECLARE_STEP_INSTANCES", INSTANCE_GROUPS),
                 ("batch", "step_batch.hpp", "LBM_DECLARE_BATCH_INSTANCES", INSTANCE_GROUPS),
                 ("step2", "step2.hpp", "LBM_DECLARE_STEP2_INSTANCES", STEP2_GROUPS),
+                ("step2b", "step2_batch.hpp", "LBM_DECLARE_STEP2_BATCH_INSTANCES", STEP2_GROUPS),
                 ("tile", "step_tile.hpp", "LBM_DECLARE_TILE_INSTANCES", TILE_GROUPS)]
     for family, header, macro, groups in families:
         for lat, types in groups:

@@ -76,6 +76,11 @@ constexpr size_t kCachedStoresTo = size_t(128) << 20;
 // Smallest boxes for which the default takes the two-step kernel (auto_kernel).
 constexpr int64_t kTwoStepSites = 64 * 64 * 64;
 constexpr int64_t kColumnsSites = 400000;
+constexpr int64_t kBatchColumnsSites = 700000;
+constexpr int64_t kBatchColumnsMean = 24 * 24 * 24;
+// Runs of the batched two-step kernel (step2_batch.hpp).
+constexpr int kRunPlanes = 16;
+constexpr int kMaxRounds = 12;
 
 // Scratch of the allocation-free residual (lbm_residual_noalloc): the
 // per-chunk partial sums of the residual kernels, 4 doubles per reduction
@@ -127,6 +132,10 @@ struct lbm_ctx {
     TileDesc* d_tiles = nullptr;
     int ntiles = 0;
     BoxDesc* d_boxes = nullptr;
+    // batched two-step tables
+    ColumnDesc* d_columns = nullptr;
+    ColumnStart* d_starts = nullptr;
+    int column_rounds = 0;
     // reductions
     ChunkDesc* d_chunks = nullptr;
     int nchunks = 0;
@@ -170,7 +179,9 @@ bool two_step_ok(const lbm_ctx* h)
 // The same kernel on columns of any size (host.hpp, columns_fit).
 bool columns_ok(const lbm_ctx* h)
 {
-    return is_single(h) && columns_fit(h->lat, h->dtype, h->dims[0], h->dims[1], h->dims[2]);
+    for (int b = 0; b < h->nbox; ++b)
+        if (!columns_fit(h->lat, h->dtype, h->dims[3 * b], h->dims[3 * b + 1], h->dims[3 * b + 2])) return false;
+    return true;
 }
 // The tile kernel has a plan for this box.
 bool tile_ok(const lbm_ctx* h) { return is_single(h) && h->tile.steps > 0; }
@@ -194,9 +205,24 @@ int auto_kernel(const lbm_ctx* h)
     return LBM_KERNEL_SCALAR;
 }
 
+// The batched two-step kernel is the default for FP32 and FP64 batches large
+// enough in all and box by box (the two rows and planes around a column cost
+// small boxes more).  D3Q19, us per step, one-step against two-step: 256 boxes of
+// sides 16-64 FP32 449 / 351 and FP64 900 / 660, 24-40 212 / 183, 16-32 93 / 89, 8-24
+// 31 / 43; 16 boxes of 16-64 (820,000 sites) 24 / 20; 16-bit storage is bound by
+// instruction issue (256 boxes of 32-64 BF16 369 / 496).
+bool batch_columns_pay(const lbm_ctx* h)
+{
+    return h->block == 0 && h->grid == 0 && h->elem >= 4 && h->nsites >= kBatchColumnsSites &&
+           h->nsites >= kBatchColumnsMean * h->nbox && columns_ok(h);
+}
+
 int effective_kernel(const lbm_ctx* h)
 {
-    if (!is_single(h)) return LBM_KERNEL_SCALAR;
+    if (!is_single(h)) {
+        if (h->kernel != LBM_KERNEL_AUTO) return h->kernel;
+        return batch_columns_pay(h) ? LBM_KERNEL_COLUMNS : LBM_KERNEL_SCALAR;
+    }
     return h->kernel == LBM_KERNEL_AUTO ? auto_kernel(h) : h->kernel;
 }
 
@@ -236,6 +262,8 @@ void free_all(lbm_ctx* h)
     }
     h->buf[0] = h->buf[1] = nullptr;
     (void)hipFree(h->d_tiles);
+    (void)hipFree(h->d_columns);
+    (void)hipFree(h->d_starts);
     (void)hipFree(h->d_boxes);
     (void)hipFree(h->d_chunks);
     (void)hipFree(h->d_box_chunk_begin);
@@ -305,6 +333,69 @@ lbm_status build_tiles(lbm_ctx* h)
             "copy tiles");
     h->ntiles = int(tiles.size());
     drop_graphs(h);
+    return LBM_OK;
+}
+
+// Columns of the batched two-step kernel and the cuts that give every block an
+// equal share of them (step2_batch.hpp).  The cost of a column-plane is its
+// rounds in both steps; a column's two extra step-1 planes count with its first.
+lbm_status build_columns(lbm_ctx* h)
+{
+    if (is_single(h) || h->d_starts) return LBM_OK;
+    std::vector<ColumnDesc> columns;
+    std::vector<int64_t> cost;  // of one plane
+    std::vector<int64_t> extra;
+    int64_t total = 0;
+    for (int b = 0; b < h->nbox; ++b) {
+        const int64_t nx = h->dims[3 * b], ny = h->dims[3 * b + 1], nz = h->dims[3 * b + 2];
+        ColumnDesc c{};
+        c.nx = int(nx);
+        c.ny = int(ny);
+        c.nz = int(nz);
+        batch_column_tile(h->elem, nx, ny, &c.tx, &c.ty);
+        c.box = b;
+        c.mem = h->mem[b];
+        c.omega = 1.0 - 1.0 / h->tau[b];
+        const int64_t r1 = column_rounds1(c.tx, c.ty), r = column_rounds(c.tx, c.ty);
+        for (c.y0 = 0; c.y0 < c.ny; c.y0 += c.ty)
+            for (c.x0 = 0; c.x0 < c.nx; c.x0 += c.tx) {
+                columns.push_back(c);
+                cost.push_back(r);
+                extra.push_back(2 * r1);
+                total += nz * r + 2 * r1;
+            }
+    }
+    // runs of about kRunPlanes planes, at most kMaxRounds a block
+    int64_t planes = 0;
+    for (const ColumnDesc& c : columns) planes += c.nz;
+    const int rounds = int(std::max<int64_t>(1, std::min<int64_t>(kMaxRounds, planes / h->cus / kRunPlanes)));
+    const int64_t grid = int64_t(h->cus) * rounds;
+    std::vector<ColumnStart> starts;
+    int64_t done = 0;
+    for (size_t c = 0; c < columns.size(); ++c) {
+        for (int z = 0; z < columns[c].nz; ++z) {
+            // run k starts at the first plane with at least k/grid of the cost before it
+            while (int64_t(starts.size()) < grid && done * grid >= int64_t(starts.size()) * total)
+                starts.push_back({int(c), z});
+            done += cost[c] + (z == 0 ? extra[c] : 0);
+        }
+    }
+    while (int64_t(starts.size()) <= grid) starts.push_back({int(columns.size()), 0});
+    ColumnDesc* dc = nullptr;
+    ColumnStart* ds = nullptr;
+    const size_t nc = columns.size() * sizeof(ColumnDesc), ns = starts.size() * sizeof(ColumnStart);
+    hipError_t e = hipMalloc(&dc, nc);
+    if (e == hipSuccess) e = hipMalloc(&ds, ns);
+    if (e == hipSuccess) e = hipMemcpy(dc, columns.data(), nc, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(ds, starts.data(), ns, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(dc);
+        (void)hipFree(ds);
+        return fail_hip(e, "column tables");
+    }
+    h->d_columns = dc;
+    h->d_starts = ds;
+    h->column_rounds = rounds;
     return LBM_OK;
 }
 
@@ -476,7 +567,6 @@ bool one_buffer(const lbm_ctx* h) { return in_place(h) || twisted(h); }
 // The two-step / tile kernel is the one in use.
 bool two_step(const lbm_ctx* h)
 {
-    if (!is_single(h)) return false;
     const int k = effective_kernel(h);
     return k == LBM_KERNEL_TWO_STEP || k == LBM_KERNEL_COLUMNS;
 }
@@ -557,6 +647,9 @@ hipError_t launch_one(lbm_ctx* h, int parity, hipStream_t s)
 // like launch_one for the buffers, two steps for the time.
 hipError_t launch_two(lbm_ctx* h, int parity, hipStream_t s)
 {
+    if (!is_single(h))
+        return launch_step2_batch(h->lattice, h->dtype, h->K, step_kind(h), h->buf[parity], h->buf[parity ^ 1],
+                                  h->d_columns, h->d_starts, h->column_rounds, h->theta, h->cus, s);
     Step2Geom geo;
     geo.nx = int(h->dims[0]);
     geo.ny = int(h->dims[1]);
@@ -651,12 +744,22 @@ lbm_status canonicalize(lbm_ctx* h)
     return LBM_OK;
 }
 
+// Tables that the kernel in use reads (batches).  Built at set-up and when the
+// kernel changes, so that a step allocates nothing.
+lbm_status build_tables(lbm_ctx* h)
+{
+    if (lbm_status st = build_tiles(h)) return st;
+    return two_step(h) ? build_columns(h) : LBM_OK;
+}
+
 // After a kernel change on an initialised handle (state natural in buf[0],
 // cur = 0): put the state into the layout the new kernel starts from.  Only
-// the twist kernel needs it (its even-time layout).
+// the twist kernel needs it (its even-time layout); a batch may need tables.
 lbm_status enter_kernel_layout(lbm_ctx* h)
 {
-    if (!h->initialized || !twisted(h)) return LBM_OK;
+    if (!h->initialized) return LBM_OK;
+    if (!is_single(h)) return build_tables(h);
+    if (!twisted(h)) return LBM_OK;
     if (lbm_status st = ensure_second(h)) return st;
     const int block = effective_block(h);
     hipError_t e = launch_relayout(h->lattice, h->dtype, kTwistEven, false, h->buf[0], h->buf[1],
@@ -683,8 +786,7 @@ lbm_status build_graph(lbm_ctx* h, int parity)
         (void)hipGraphExecDestroy(h->gexec[parity]);
         h->gexec[parity] = nullptr;
     }
-    lbm_status st = build_tiles(h);
-    if (st != LBM_OK) return st;
+    if (lbm_status st = build_tables(h)) return st;
     HIP_TRY(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
     hipError_t le = hipSuccess;
     int p = parity;
@@ -892,8 +994,8 @@ lbm_status lbm_set_kernel(lbm_t h, int32_t kernel)
                         "multiple of %d and one z-plane of populations below 2 GiB",
                         kTwoStepTileX, two_step_tile_y(h->elem));
         if (kernel == LBM_KERNEL_COLUMNS && !columns_ok(h))
-            return fail(LBM_EINVAL, "the two-step kernel on columns needs a single D3Q15 or D3Q19 box and one z-plane "
-                                    "of populations below 2 GiB");
+            return fail(LBM_EINVAL, "the two-step kernel on columns needs D3Q15 or D3Q19 and one z-plane of "
+                                    "populations below 2 GiB");
         if (kernel == LBM_KERNEL_TILE && !tile_ok(h))
             return fail(LBM_EINVAL, "the tile kernel needs a single D2Q9, D3Q15 or D3Q19 box for which it has a plan");
         if ((kernel == LBM_KERNEL_IN_PLACE || kernel == LBM_KERNEL_TWIST) && !is_single(h))
@@ -923,7 +1025,7 @@ lbm_status lbm_init(lbm_t h, const double* rho, const double* u, int32_t on_devi
         if (!rho || !u) return fail(LBM_EINVAL, "rho or u is NULL");
         HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
         if (lbm_status st = ensure_buffers(h)) return st;
-        if (lbm_status st = build_tiles(h)) return st;
+        if (lbm_status st = build_tables(h)) return st;
         if (lbm_status st = clear_padding(h)) return st;
         const size_t n = size_t(h->nsites);
         double *drho = nullptr, *du = nullptr;
@@ -979,7 +1081,7 @@ lbm_status lbm_step(lbm_t h, int64_t n)
         HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
         if (!one_buffer(h))
             if (lbm_status st = ensure_second(h)) return st;
-        if (lbm_status st = build_tiles(h)) return st;
+        if (lbm_status st = build_tables(h)) return st;
         const int G = graph_steps(h);
         int64_t left = n;
         if (G > 1) {
@@ -1080,10 +1182,7 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
             if (tile_ok(h)) {
                 cand.push_back({LBM_KERNEL_TILE, 0, 0});
             } else if (columns_ok(h)) {
-                // the two-step kernel at one and two blocks per compute unit
-                const int k = two_step_ok(h) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_COLUMNS;
-                cand.push_back({k, 0, 0});
-                cand.push_back({k, 0, 2 * h->cus});
+                cand.push_back({two_step_ok(h) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_COLUMNS, 0, 0});
             } else {
                 // one-step forms that were never the fastest where one of the
                 // above runs
@@ -1091,8 +1190,10 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
                 if (row_wave_sites(h)) cand.push_back({LBM_KERNEL_ROW_WAVE, 0, 0});
             }
         } else {
-            for (int b : {64, 128, 256})
-                for (int g : {0, 1024, 2048, 4096}) cand.push_back({LBM_KERNEL_SCALAR, b, g});
+            // (persistent grids trail one wave per tile, 68% against 75% of the
+            // HBM peak on 256 boxes, and are not timed)
+            for (int b : {64, 128, 256}) cand.push_back({LBM_KERNEL_SCALAR, b, 0});
+            if (columns_ok(h)) cand.push_back({LBM_KERNEL_COLUMNS, 0, 0});
         }
 
         // tuning steps the state: keep a copy and restore it afterwards; the
@@ -1383,7 +1484,7 @@ lbm_status lbm_set_state(lbm_t h, const void* buf, size_t bytes)
         std::memcpy(&hd, buf, sizeof(hd));
         HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
         if (lbm_status st = ensure_buffers(h)) return st;
-        if (lbm_status st = build_tiles(h)) return st;
+        if (lbm_status st = build_tables(h)) return st;
         const char* src = static_cast<const char*>(buf) + sizeof(hd);
         if (lbm_status st = clear_padding(h)) return st;
         const size_t payload = size_t(h->lat.Q) * size_t(h->nstored) * h->elem;
@@ -1432,7 +1533,7 @@ lbm_status lbm_get_info(lbm_t h, lbm_info* info)
         info->bytes_per_site_update = int64_t(2 * h->lat.Q) * int64_t(h->elem);
         info->state_bytes = h->state_bytes;
         info->block = effective_block(h);
-        info->grid = two_step(h) ? two_step_grid(h) : h->grid;
+        info->grid = (two_step(h) && is_single(h)) ? two_step_grid(h) : h->grid;
         info->graph_chunk = h->graph_chunk;
         info->kernel = effective_kernel(h);
         info->collision = h->collision;

@@ -128,6 +128,21 @@ void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
     *ty = even_piece(ny, two_step_threads(elem) / (*tx + 2) - 2);
 }
 
+void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
+{
+    *tx = even_piece(nx, 128);
+    const int64_t most = std::min<int64_t>(ny, batch_columns_threads(elem) / (*tx + 2) - 2);
+    int64_t best = 0;
+    for (int64_t t = most; t >= 1; --t) {
+        const int piece = even_piece(ny, t);
+        const int64_t cost = (ny + piece - 1) / piece * column_rounds(*tx, piece);
+        if (t == most || cost < best) {
+            best = cost;
+            *ty = piece;
+        }
+    }
+}
+
 int64_t tile_region(const LatticeInfo& L, const TilePlan& p, int64_t nx, int steps)
 {
     const int64_t g = 2 * (steps - 1);

@@ -56,6 +56,12 @@ constexpr int two_step_threads(size_t elem)
     return ((kTwoStepTileX + 2) * (two_step_tile_y(elem) + 2) + 63) / 64 * 64;
 }
 
+// Threads of a block of the batched two-step kernel (step2_batch.hpp).  FP64:
+// what its two LDS planes leave room for (448 threads: 756 against 720 us per
+// step of 256 boxes of sides 16-64, 4 rounds).  Else 704: 1024 would fit too,
+// but ran at 360 us against 351 (8 rounds).
+constexpr int batch_columns_threads(size_t elem) { return elem == 8 ? 512 : 704; }
+
 // Whether the two-step kernel applies to a single nx x ny x nz box: a 3-D
 // lattice whose velocity components are at most 1 in magnitude (a one-site
 // ring), nx and ny multiples of the tile, and one z-plane of populations
@@ -76,6 +82,16 @@ bool columns_fit(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
 // 8); 160^3 83 (80 x 6 and 160 x 2), 93 (32 x 18); FP64 100^3 38 (100 x 2), 44
 // (50 x 6).
 void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
+
+// Rounds of a compute unit's four SIMDs that a plane of a column tile takes:
+// waves of step 1 and of step 2, four at a time.
+constexpr int column_rounds1(int tx, int ty) { return ((tx + 2) * (ty + 2) + 255) / 256; }
+constexpr int column_rounds(int tx, int ty) { return column_rounds1(tx, ty) + (tx * ty + 255) / 256; }
+
+// Column tile of the batched two-step kernel: x in even pieces of at most 128,
+// and the rows that take the fewest rounds over the box, since the busiest
+// SIMD sets the time of a plane.
+void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 
 constexpr int kTileMaxSteps = 16;
 constexpr int64_t kTileMaxLds = 160 * 1024;  // a compute unit's LDS

@@ -80,6 +80,23 @@ struct alignas(64) TileDesc {
 };
 static_assert(sizeof(TileDesc) == 64, "tile descriptor is one scalar load");
 
+// A column of the batched two-step kernel (step2_batch.hpp): sites x0 .. x0 + tx,
+// y0 .. y0 + ty of box `box` (cut at its edges), every z, with the box's
+// geometry, population offset and relaxation factor.
+struct alignas(64) ColumnDesc {
+    int nx, ny, nz;
+    int x0, y0, tx, ty;
+    int box;
+    long long mem;
+    double omega;
+};
+static_assert(sizeof(ColumnDesc) == 64, "column descriptor is one scalar load");
+
+// Where a run of that kernel starts, and the one before it ends.
+struct ColumnStart {
+    int column, z;
+};
+
 // Population layout of a box: its local sites l = (z * ny + y) * nx + x are
 // cut into blocks of w consecutive sites, and block l / w holds Q runs of w
 // values, population i of site l at element
@@ -146,6 +163,11 @@ hipError_t launch_step_vec(int lat, int dtype, int K, int kind, const void* src,
 // multiple of 64, so populations with c_x = 0 are read in whole blocks.
 hipError_t launch_step_batch(int lat, int dtype, int K, int kind, const void* src, void* dst, const TileDesc* tiles,
                              int ntiles, double theta, int block, int grid, bool aligned_rows, hipStream_t s);
+// Two steps of a batch in one launch (step2_batch.hpp) on `grid` blocks, starts
+// holding grid * rounds + 1 entries; D3Q15 and D3Q19 only, else hipErrorInvalidValue.
+hipError_t launch_step2_batch(int lat, int dtype, int K, int kind, const void* src, void* dst,
+                              const ColumnDesc* columns, const ColumnStart* starts, int rounds, double theta,
+                              int grid, hipStream_t s);
 // Readers of the stored state, in any StateLayout (the in-place layouts for
 // a single box only).
 hipError_t launch_moments(int lat, int dtype, const void* src, int layout, double* rho, double* u,

@@ -534,6 +534,20 @@ hipError_t launch_step2(int lat, int dtype, int K, int kind, const void* src, vo
     });
 }
 
+hipError_t launch_step2_batch(int lat, int dtype, int K, int kind, const void* src, void* dst,
+                              const ColumnDesc* columns, const ColumnStart* starts, int rounds, double theta,
+                              int grid, hipStream_t s)
+{
+    return by_pair(lat, dtype, [&](auto Lt, auto* Sp) -> hipError_t {
+        using L = decltype(Lt);
+        using S = std::remove_pointer_t<decltype(Sp)>;
+        if constexpr (std::is_same<L, D3Q15>::value || std::is_same<L, D3Q19>::value)
+            return launch_step2_batch_l<L, S>(K, kind, src, dst, columns, starts, rounds, theta, grid, s);
+        else
+            return hipErrorInvalidValue;
+    });
+}
+
 hipError_t launch_step_tile(int lat, int dtype, int K, int kind, const void* src, void* dst, const TileGeom& geo,
                             double omega, double theta, hipStream_t s)
 {

@@ -60,6 +60,73 @@ constexpr int step2_threads()
     return two_step_threads(sizeof(S));
 }
 
+// Walks a column of planes za .. zb - 1: pull(p, g) loads the step-1 inputs of
+// the thread's site at plane p, put(p, h) stores the owner's step-2 results;
+// ohy: the owner's site in an LDS plane, one row up, its own and one row down.
+template <class L, class S, int K, int KIND, bool BATCH, int NT, class Pull, class Put>
+__device__ __forceinline__ void walk_column(S (&lplane)[2][L::Q][NT], int za, int zb, bool owner, const int (&ohy)[3],
+                                            typename Store<S>::R omega, typename Store<S>::R theta, Pull&& pull,
+                                            Put&& put)
+{
+    using ST = Store<S>;
+    using R = typename ST::R;
+    constexpr bool PROJ = !std::is_same<R, double>::value;
+    constexpr int Q = L::Q;
+    const int tid = threadIdx.x;
+    // When the next plane's loads are issued: before this plane's step 1 into
+    // registers of their own, or after it into its own (LATE_LOADS), which saves
+    // Q moves a plane and Q registers but leaves only step 2 to hide the
+    // latency.  Measured on D3Q19 256^3, us per step, early against late: FP64
+    // 490 / 474, FP16 220 / 209, FP32 248 / 260, BF16 222 / 231, energy flux 287 /
+    // 286; the batched kernel (256 boxes of sides 16-64, FP32) 447 / 411.
+    constexpr bool LATE_LOADS = BATCH || std::is_same<S, double>::value || std::is_same<S, _Float16>::value;
+    // held LDS values: read from the first plane on, used from the third
+    // (k >= 2); zeroed so that no read is of an indeterminate value
+    R g[Q], hold0[Q] = {}, hold1a[Q] = {}, hold1b[Q] = {};
+    [[maybe_unused]] R next[Q];
+    const int planes = zb - za + 2;  // step-1 planes za - 1 .. zb
+    if constexpr (LATE_LOADS) pull(za - 1, g);
+    else pull(za - 1, next);
+    for (int k = 0; k < planes; ++k) {
+        const int p = za - 1 + k;
+        if constexpr (!LATE_LOADS) {
+            unroll<Q>([&](auto I) { g[decltype(I)::value] = next[decltype(I)::value]; });
+            if (k + 1 < planes) pull(p + 1, next);
+        }
+        collide_site<L, K, KIND, PROJ, R>(g, omega, theta);
+        S(&buf)[Q][NT] = lplane[k & 1];
+        unroll<Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            ST::put(&buf[i][tid], g[i]);
+        });
+        if constexpr (LATE_LOADS)
+            if (k + 1 < planes) pull(p + 1, g);
+        __syncthreads();
+        if (owner) {
+            R h[Q];
+            unroll<Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+                const R v = ST::get(&buf[i][0] + (ohy[1 - cy] - cx));
+                if constexpr (cz == -1) {
+                    h[i] = v;
+                } else if constexpr (cz == 0) {
+                    h[i] = hold0[i];
+                    hold0[i] = v;
+                } else {
+                    h[i] = hold1b[i];
+                    hold1b[i] = hold1a[i];
+                    hold1a[i] = v;
+                }
+            });
+            if (k >= 2) {  // plane p - 1 has all its inputs
+                collide_site<L, K, KIND, PROJ, R>(h, omega, theta);
+                put(p - 1, h);
+            }
+        }
+    }
+}
+
 template <class L, class S, int K, int KIND, bool CACHED_STORES>
 __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __restrict__ src, S* __restrict__ dst,
                                                                  Step2Geom geo, typename Store<S>::R omega,
@@ -67,7 +134,6 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
 {
     using ST = Store<S>;
     using R = typename ST::R;
-    constexpr bool PROJ = !std::is_same<R, double>::value;
     constexpr int Q = L::Q;
     constexpr int NT = step2_threads<S>();
     static_assert(L::D == 3 && L::R == 1, "a one-site ring in x, y and z");
@@ -81,13 +147,6 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
     // first: its 20-60 fewer registers per lane keep it from spilling (330
     // against 400 us per FP32 step).
     constexpr bool SCALAR_BASE = sizeof(S) == 8 || KIND == kFilteredQ;
-    // When the next plane's loads are issued: before this plane's step 1 into
-    // registers of their own, or after it into its own (LATE_LOADS), which saves
-    // Q moves a plane and Q registers but leaves only step 2 to hide the
-    // latency.  Measured on D3Q19 256^3, us per step, early against late: FP64
-    // 490 / 474, FP16 220 / 209, FP32 248 / 260, BF16 222 / 231, energy flux 287 /
-    // 286.
-    constexpr bool LATE_LOADS = std::is_same<S, double>::value || std::is_same<S, _Float16>::value;
     __shared__ S lplane[2][Q][NT];
 
     const int tid = threadIdx.x;
@@ -145,63 +204,22 @@ __global__ __launch_bounds__(step2_threads<S>(), 2) void k_step2(const S* __rest
             });
         };
 
-        // held LDS values: read from the first plane on, used from the third
-        // (k >= 2); zeroed so that no read is of an indeterminate value
-        R g[Q], hold0[Q] = {}, hold1a[Q] = {}, hold1b[Q] = {};
-        [[maybe_unused]] R next[Q];
-        const int planes = zb - za + 2;  // step-1 planes za - 1 .. zb
-        if constexpr (LATE_LOADS) pull(za - 1, g);
-        else pull(za - 1, next);
-        for (int k = 0; k < planes; ++k) {
-            const int p = za - 1 + k;
-            if constexpr (!LATE_LOADS) {
-                unroll<Q>([&](auto I) { g[decltype(I)::value] = next[decltype(I)::value]; });
-                if (k + 1 < planes) pull(p + 1, next);
-            }
-            collide_site<L, K, KIND, PROJ, R>(g, omega, theta);
-            S(&buf)[Q][NT] = lplane[k & 1];
-            unroll<Q>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                ST::put(&buf[i][tid], g[i]);
+        auto put = [&](int p, const R(&h)[Q]) {
+            if (!writer) return;
+            char* out = reinterpret_cast<char*>(dst) + (long long)wrap_coord(p, geo.nz) * plane_bytes;
+            unroll<Q>([&](auto M) {
+                constexpr int m = decltype(M)::value;
+                constexpr int i = mem_pop<L>(m);
+                char* p8;
+                if constexpr (SCALAR_BASE)
+                    p8 = (out + (long long)m * row_bytes) + own;
+                else
+                    p8 = out + (own + unsigned(m) * row_bytes);
+                if constexpr (CACHED_STORES) ST::put(reinterpret_cast<S*>(p8), h[i]);
+                else ST::put_nt(reinterpret_cast<S*>(p8), h[i]);
             });
-            if constexpr (LATE_LOADS)
-                if (k + 1 < planes) pull(p + 1, g);
-            __syncthreads();
-            if (owner) {
-                R h[Q];
-                unroll<Q>([&](auto I) {
-                    constexpr int i = decltype(I)::value;
-                    constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-                    const R v = ST::get(&buf[i][0] + (ohy[1 - cy] - cx));
-                    if constexpr (cz == -1) {
-                        h[i] = v;
-                    } else if constexpr (cz == 0) {
-                        h[i] = hold0[i];
-                        hold0[i] = v;
-                    } else {
-                        h[i] = hold1b[i];
-                        hold1b[i] = hold1a[i];
-                        hold1a[i] = v;
-                    }
-                });
-                if (k >= 2) {  // plane p - 1 has all its inputs
-                    collide_site<L, K, KIND, PROJ, R>(h, omega, theta);
-                    char* out = reinterpret_cast<char*>(dst) + (long long)wrap_coord(p - 1, geo.nz) * plane_bytes;
-                    if (writer)
-                        unroll<Q>([&](auto M) {
-                            constexpr int m = decltype(M)::value;
-                            constexpr int i = mem_pop<L>(m);
-                            char* p8;
-                            if constexpr (SCALAR_BASE)
-                                p8 = (out + (long long)m * row_bytes) + own;
-                            else
-                                p8 = out + (own + unsigned(m) * row_bytes);
-                            if constexpr (CACHED_STORES) ST::put(reinterpret_cast<S*>(p8), h[i]);
-                            else ST::put_nt(reinterpret_cast<S*>(p8), h[i]);
-                        });
-                }
-            }
-        }
+        };
+        walk_column<L, S, K, KIND, false>(lplane, za, zb, owner, ohy, omega, theta, pull, put);
         __syncthreads();  // the next segment's first plane refills buffer 0
     }
 }

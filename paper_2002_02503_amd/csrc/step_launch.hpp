@@ -57,6 +57,11 @@ template <class L, class S>
 hipError_t launch_step_batch_l(int K, int kind, const void* src, void* dst, const TileDesc* tiles, int ntiles,
                                double theta, int block, int grid, bool aligned_rows, hipStream_t s);
 
+// Batch, two steps per launch (3-D lattices with a one-site ring only).
+template <class L, class S>
+hipError_t launch_step2_batch_l(int K, int kind, const void* src, void* dst, const ColumnDesc* columns,
+                                const ColumnStart* starts, int rounds, double theta, int grid, hipStream_t s);
+
 #define LBM_DECLARE_STEP_INSTANCES(EXT, L, S)                                                                    \
     EXT template hipError_t launch_step_l<L, S>(int, int, const void*, void*, const StepGeom&, double, double,  \
                                                 int, bool, hipStream_t);                                       \
@@ -71,6 +76,10 @@ hipError_t launch_step_batch_l(int K, int kind, const void* src, void* dst, cons
 #define LBM_DECLARE_STEP2_INSTANCES(EXT, L, S)                                                                 \
     EXT template hipError_t launch_step2_l<L, S>(int, int, const void*, void*, const Step2Geom&, double, double, \
                                                  int, hipStream_t);
+
+#define LBM_DECLARE_STEP2_BATCH_INSTANCES(EXT, L, S)                                                           \
+    EXT template hipError_t launch_step2_batch_l<L, S>(int, int, const void*, void*, const ColumnDesc*,       \
+                                                       const ColumnStart*, int, double, int, hipStream_t);
 
 #define LBM_DECLARE_TILE_INSTANCES(EXT, L, S)                                                                  \
     EXT template hipError_t launch_step_tile_l<L, S>(int, int, const void*, void*, const TileGeom&, double,    \
@@ -108,6 +117,15 @@ LBM_EXTERN_LATTICE(D3Q19)
 LBM_EXTERN_LATTICE(D3Q39)
 LBM_EXTERN_STEP2(D3Q15)
 LBM_EXTERN_STEP2(D3Q19)
+
+#define LBM_EXTERN_STEP2_BATCH(L)                            \
+    LBM_DECLARE_STEP2_BATCH_INSTANCES(extern, L, double)     \
+    LBM_DECLARE_STEP2_BATCH_INSTANCES(extern, L, float)      \
+    LBM_DECLARE_STEP2_BATCH_INSTANCES(extern, L, _Float16)   \
+    LBM_DECLARE_STEP2_BATCH_INSTANCES(extern, L, bf16_t)
+
+LBM_EXTERN_STEP2_BATCH(D3Q15)
+LBM_EXTERN_STEP2_BATCH(D3Q19)
 LBM_EXTERN_TILE(D2Q9)
 LBM_EXTERN_TILE(D3Q15)
 LBM_EXTERN_TILE(D3Q19)

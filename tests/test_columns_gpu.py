@@ -62,3 +62,54 @@ def test_columns_refusals_and_the_default_choice():
                               ((100, 100, 100), "bf16", "columns"), ((128, 128, 128), "fp16", "scalar"), ((65, 65, 65), "fp32", "scalar")]:
         with lbm.Simulation("D3Q19", dims, 0.8, dtype=dtype, torch_memory=False) as sim:
             assert names[sim.info()["kernel"]] == want, (dims, dtype)
+
+
+def _batch(lattice, dims, taus, dtype, seed, steps, kernel, **kw):
+    from paper_2002_02503_amd import lbm
+
+    rng = np.random.default_rng(seed)
+    n = sum(a * b * c for a, b, c in dims)
+    rho, u = 1.0 + rng.uniform(-0.01, 0.01, size=n), rng.uniform(-0.05, 0.05, size=(3, n))
+    with lbm.Simulation(lattice, dims, taus, dtype=dtype, kernel=kernel, **kw) as sim:
+        sim.init(rho, u)
+        out = []
+        for k in steps:
+            out += sim.step(k).moments()
+        return out + [sim.get_state()]
+
+
+BATCHES = [
+    # whole rows and pieces of them, sides of one to three sites, several columns a box
+    ("D3Q19", [(40, 37, 9), (1, 1, 1), (2, 3, 5), (3, 2, 1), (200, 11, 4), (64, 30, 6)], "fp32", {"theta": 0.5}),
+    ("D3Q19", [(40, 37, 9), (7, 5, 300), (129, 6, 3)], "fp64", {}),
+    ("D3Q19", [(16, 64, 20), (33, 17, 9)], "fp16", {"K": 2}),
+    ("D3Q15", [(20, 30, 10), (61, 29, 8)], "bf16", {"collision": "bgk"}),
+    # more planes than blocks: two runs a block
+    ("D3Q15", [(5, 4, 40 + k % 3) for k in range(300)], "fp32", {}),
+]
+
+
+@pytest.mark.parametrize("lattice,dims,dtype,kw", BATCHES)
+def test_batched_columns_equal_the_one_step_kernel(lattice, dims, dtype, kw):
+    """The same bits and checkpoints after odd and even counts, in graphs
+    replayed around reads of the state."""
+    taus = [0.55 + 0.01 * (k % 40) for k in range(len(dims))]
+    a = _batch(lattice, dims, taus, dtype, len(dims), (1, 2, 9, 8), "columns", graph_chunk=4, **kw)
+    b = _batch(lattice, dims, taus, dtype, len(dims), (1, 2, 9, 8), "scalar", graph_chunk=1, **kw)
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+def test_batched_columns_choice():
+    from paper_2002_02503_amd import lbm
+
+    def kernel_of(lattice, dims, dtype, **kw):
+        with lbm.Simulation(lattice, dims, [0.7] * len(dims), dtype=dtype, torch_memory=False, **kw) as sim:
+            return {v: k for k, v in lbm.KERNELS.items()}[sim.info()["kernel"]]
+
+    big, small = [(60, 50, 40)] * 8, [(20, 20, 20)] * 200
+    assert kernel_of("D3Q19", big, "fp32") == "columns" and kernel_of("D3Q19", big, "fp64") == "columns"
+    assert kernel_of("D3Q19", big, "fp16") == "scalar" and kernel_of("D3Q19", small, "fp32") == "scalar"
+    assert kernel_of("D3Q19", big, "fp32", block=128) == "scalar" and kernel_of("D3Q39", big, "fp32") == "scalar"
+    with pytest.raises(lbm.LBMError) as e:
+        lbm.Simulation("D3Q39", [(8, 8, 8), (9, 9, 9)], [0.6, 0.7], kernel="columns", torch_memory=False)
+    assert e.value.name == "LBM_EINVAL"
