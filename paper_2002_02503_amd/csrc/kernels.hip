@@ -130,8 +130,8 @@ __global__ __launch_bounds__(256) void k_init(const double* __restrict__ rho, co
 // rho - 1 and rho u (eq. mme) of one stored site, in double (outside the
 // step, for output and reductions).  `p` points at population 0 of the site,
 // w is the block width of the box's layout.
-// NT: non-temporal loads, for the reductions (the state is read once).
-template <class L, class S, bool NT>
+// The state is read once: non-temporal loads.
+template <class L, class S>
 __device__ __forceinline__ void site_moments(const S* __restrict__ p, int w, double& dsum, double (&j)[3])
 {
     using ST = Store<S>;
@@ -141,7 +141,7 @@ __device__ __forceinline__ void site_moments(const S* __restrict__ p, int w, dou
         constexpr int i = decltype(I)::value;
         constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
         constexpr int m = mem_row<L>(i);
-        const double gi = double(NT ? ST::get_nt(p + (long long)m * w) : ST::get(p + (long long)m * w));
+        const double gi = double(ST::get_nt(p + (long long)m * w));
         dsum += gi;
         if constexpr (cx != 0) j[0] += double(cx) * gi;
         if constexpr (cy != 0) j[1] += double(cy) * gi;
@@ -179,19 +179,21 @@ __device__ __forceinline__ void relaid_site_moments(const S* __restrict__ base, 
     if constexpr (L::D == 3) j[2] = over<L::S>(j[2]);
 }
 
-template <class L, class S, int LAYOUT, bool NT>
+template <class L, class S, int LAYOUT>
 __device__ __forceinline__ void stored_site_moments(const S* __restrict__ base, const ChunkDesc& ch, int k,
                                                     const BoxDesc& b, double& dsum, double (&j)[3])
 {
     const SitePos pos = locate<LAYOUT != kNatural>(ch, k, b);
     if constexpr (LAYOUT != kNatural) relaid_site_moments<L, S, LAYOUT>(base, pos, b, dsum, j);
-    else site_moments<L, S, NT>(base + site_elem<L::Q>(pos, b.w), b.w, dsum, j);
+    else site_moments<L, S>(base + site_elem<L::Q>(pos, b.w), b.w, dsum, j);
 }
 
-// Bound by HBM.  The fields are written non-temporally and the state read with
-// cached loads: D3Q19 256^3, us a call (natural layout FP32, FP64 and, twisted,
-// FP32): cached stores 367, 629, 359; non-temporal loads and stores 374, 603;
-// non-temporal stores alone 337 (twisted).
+// Bound by HBM.  From the natural layout the state is read and the fields are
+// written non-temporally: D3Q19 256^3, us a call, FP32 / FP16 / FP64: 315 / 211 /
+// 563, with cached loads 338 / 220 / 585, with cached stores 346 / 223 / 584, with
+// both cached 361 / 243 / 609.  The in-place layouts, whose cells are shared
+// between sites, keep the default policy (FP32 twisted 359-370, non-temporal
+// stores 375).
 template <class L, class S, int LAYOUT>
 __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ src, double* __restrict__ rho,
                                                  double* __restrict__ u, const ChunkDesc* __restrict__ chunks,
@@ -204,11 +206,15 @@ __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ src, doub
     if (k >= ch.count) return;
     const long long s = ch.start + k;
     double d, j[3];
-    stored_site_moments<L, S, LAYOUT, false>(base, ch, k, b, d, j);
+    stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
     const double r = 1.0 + d;
-    __builtin_nontemporal_store(r, rho + s);
+    auto put = [](double* q, double v) {
+        if constexpr (LAYOUT == kNatural) __builtin_nontemporal_store(v, q);
+        else *q = v;
+    };
+    put(rho + s, r);
 #pragma unroll
-    for (int a = 0; a < L::D; ++a) __builtin_nontemporal_store(j[a] / r, u + a * nsites + s);
+    for (int a = 0; a < L::D; ++a) put(u + a * nsites + s, j[a] / r);
 }
 
 // ---------------------------------------------------------------------------
@@ -252,7 +258,7 @@ __global__ __launch_bounds__(kRedBlock) void k_totals_partial(const S* __restric
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int k = threadIdx.x; k < ch.count; k += kRedBlock) {
         double d, j[3];
-        stored_site_moments<L, S, LAYOUT, true>(base, ch, k, b, d, j);
+        stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
         acc[0] += d;
         acc[1] += j[0];
         acc[2] += j[1];
@@ -300,7 +306,7 @@ __global__ __launch_bounds__(kRedBlock) void k_residual_partial(const S* __restr
     for (int k = threadIdx.x; k < ch.count; k += kRedBlock) {
         const long long s = ch.start + k;
         double d, j[3];
-        stored_site_moments<L, S, LAYOUT, true>(base, ch, k, b, d, j);
+        stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
         const double r = 1.0 + d;
 #pragma unroll
         for (int a = 0; a < L::D; ++a) {
