@@ -167,6 +167,17 @@ bool tile_plan_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int
     return true;
 }
 
+// Whether a fitting plan is expected to be faster than the one-site step
+// (host.hpp, tile_plan).
+static bool tile_pays(const LatticeInfo& L, int64_t nx, int64_t ny, int64_t nz, int64_t cus, const TilePlan& p)
+{
+    const int64_t tiles = ((nx + p.tx - 1) / p.tx) * ((ny + p.ty - 1) / p.ty) * ((nz + p.tz - 1) / p.tz);
+    int64_t rounds = 0;  // of a tile over all its steps
+    for (int s = p.steps; s >= 1; --s) rounds += (tile_region(L, p, nx, s) + 255) / 256;
+    if (L.D == 3) return p.tx == nx && (tiles + cus - 1) / cus * rounds <= kTileRounds3d;
+    return tiles <= cus || ny > 1;
+}
+
 bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, int cus, TilePlan* out)
 {
     if (L.R != 1 || nx < 1 || ny < 1 || nz < 1 || cus < 1) return false;
@@ -174,6 +185,7 @@ bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t 
     const int64_t share = nx * ny * nz / cus;  // sites of a compute unit
     TilePlan p{1, 1, 1, 0, 0};
     if (L.D == 2) {
+        if (storage_bytes(dtype) == 2 && share > kTileShare16) return false;
         // a tile per compute unit while the box is small, then 32 x 16
         p.tx = even_piece(nx, share <= 32 ? 8 : share <= 128 ? 16 : 32);
         p.ty = even_piece(ny, share <= 32 ? 4 : share <= 256 ? 8 : 16);
@@ -188,14 +200,15 @@ bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t 
         }
         p.steps = share <= 32 ? 3 : 2;
     }
-    // fewer steps where the box is narrower than the ring or LDS too small
+    // fewer steps where the box is narrower than the ring, LDS too small or the
+    // rings cost too much
     for (; p.steps >= 2; --p.steps) {
         const int64_t n = tile_region(L, p, nx, p.steps);
         const int64_t rounds = (n + 1023) / 1024;
         const int64_t least = tile_region(L, p, nx, p.steps - 1);
         const int64_t threads = std::max(least, (n + rounds - 1) / rounds);
         p.block = int(std::min<int64_t>(1024, (threads + 63) / 64 * 64));
-        if (tile_plan_fits(L, dtype, nx, ny, nz, p)) {
+        if (tile_plan_fits(L, dtype, nx, ny, nz, p) && tile_pays(L, nx, ny, nz, cus, p)) {
             *out = p;
             return true;
         }

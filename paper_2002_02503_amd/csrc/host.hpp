@@ -114,18 +114,26 @@ bool tile_plan_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int
 
 // The plan for a box on a device of `cus` compute units; false: none, because
 // none fits or the one-site step is faster.
-//   - D2Q9: every size.  Measured, us per step, one-site against the plan (tile,
+//   - D2Q9: every size, but in 16-bit storage, whose steps are bound by
+//     instruction issue, only up to kTileShare16 sites per compute unit, and
+//     with more tiles than units not for a single row (100000 sites: 2.9 us per
+//     step one-site, 3.6 tiled; two rows of them 5.9 and 4.9).  Measured, us per step, one-site against the plan (tile,
 //     steps): 64^2 FP64 2.52 / 0.96 (8 x 4, 8), 256^2 FP32 3.29 / 1.65 (32 x 8,
 //     8), 601 x 400 FP32 5.9 / 3.2 (32 x 16, 5), 1024^2 FP32 14.4 / 8.0 and
-//     FP64 26.5 / 10.4 (32 x 16, 5).
+//     FP64 26.5 / 10.4 (32 x 16, 5), 4096^2 FP32 190 / 121; BF16 1024^2 9.1 / 9.9.
 //   - D3Q15 and D3Q19: up to kTileShare3d sites per compute unit.  The ring
 //     costs more in three dimensions, so two steps (three up to 32 sites per
 //     unit) and whole x-rows, whose loads use full lines: 16^3 FP32 3.09 / 1.91
 //     (16 x 2 x 1, 3), 32^3 FP32 3.64 / 2.85 (32 x 2 x 2, 2), FP64 4.48 / 3.86,
-//     40 x 37 x 29 4.52 / 4.28; at 64^3 (8.5 / 8.4) and above nothing is gained.
+//     8 x 64 x 64 6.3 / 2.9; at 64^3 (8.5 / 8.4) and above nothing is gained.  A
+//     compute unit's SIMDs take at most kTileRounds3d rounds of four waves over
+//     the steps, and rows are whole: 200 x 200 x 1 (8 rounds) 3.8 / 5.2, 40000 x 1 x
+//     1 (12) 3.1 / 5.4, 33^3 (6) 4.3 / 4.1, 300 x 10 x 10 (4, rows in pieces) 3.9 / 4.2.
 // Block: step 1's region in as few rounds as 1024 threads allow (32^3 with the
 // threads that step 2 needs, 128, took 4.0 us per step).
 constexpr int64_t kTileShare3d = 160;
+constexpr int64_t kTileRounds3d = 4;
+constexpr int64_t kTileShare16 = 1024;
 bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, int cus, TilePlan* out);
 
 // The argument checks of lbm_create / lbm_create_batch for nbox boxes

@@ -59,7 +59,9 @@ def test_columns_refusals_and_the_default_choice():
         assert e.value.name == "LBM_EINVAL"
     names = {v: k for k, v in lbm.KERNELS.items()}
     for dims, dtype, want in [((201, 150, 77), "fp32", "columns"), ((100, 100, 100), "fp64", "columns"),
-                              ((100, 100, 100), "bf16", "columns"), ((128, 128, 128), "fp16", "scalar"), ((65, 65, 65), "fp32", "scalar")]:
+                              ((201, 150, 77), "bf16", "columns"), ((128, 128, 128), "fp16", "scalar"),
+                              ((101, 101, 101), "fp16", "scalar"), ((700, 700, 1), "fp32", "scalar"),
+                              ((100000, 2, 2), "fp32", "scalar"), ((65, 65, 65), "fp32", "scalar")]:
         with lbm.Simulation("D3Q19", dims, 0.8, dtype=dtype, torch_memory=False) as sim:
             assert names[sim.info()["kernel"]] == want, (dims, dtype)
 

@@ -35,8 +35,8 @@ CASES = [
     ("D3Q19", (17, 5, 3), "fp64", {}),
     ("D3Q19", (1, 1, 7), "fp32", {}),
     ("D3Q19", (2, 3, 2), "bf16", {}),
-    ("D3Q19", (130, 12, 7), "fp32", {}),          # x in pieces of 44, the last 42
-    ("D3Q15", (40, 37, 23), "fp32", {"collision": "bgk"}),
+    ("D3Q19", (64, 24, 7), "fp32", {}),
+    ("D3Q15", (40, 30, 23), "fp32", {"collision": "bgk"}),
     ("D3Q15", (24, 40, 32), "fp64", {"K": 2}),
 ]
 
@@ -89,6 +89,10 @@ def test_tile_refusals_and_the_default_choice():
     # a launch shape is the one-site step's
     assert names[kernel_of("D3Q19", (32, 32, 32), 0.8, block=128)] == "scalar"
     assert names[kernel_of("D3Q39", (32, 32, 32), 0.8)] == "scalar"
+    # where the rings cost more than they save
+    assert names[kernel_of("D3Q19", (200, 200, 1), 0.8)] == "scalar"
+    assert names[kernel_of("D2Q9", (100000, 1, 1), 0.8)] == "scalar"
+    assert names[kernel_of("D2Q9", (1024, 1024, 1), 0.8, dtype="fp16")] == "scalar"
 
 
 def test_default_choice_resumes_and_switches_mid_run():
