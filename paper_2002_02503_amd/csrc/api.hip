@@ -146,6 +146,7 @@ struct lbm_ctx {
     int* d_box_chunk_begin = nullptr;
     double* d_partial = nullptr;
     double* d_out = nullptr;
+    bool keep_parity = false;       // a caller captured steps (keep_parity below)
     // captured step graphs, one per starting buffer
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gexec_steps[2] = {0, 0};
@@ -720,6 +721,24 @@ int graph_steps(const lbm_ctx* h)
     return (tiled(h) && h->graph_chunk > m) ? h->graph_chunk - h->graph_chunk % m : h->graph_chunk;
 }
 
+// A graph that the caller captures from lbm_step replays from the buffer that
+// was current then.  With one step per launch an even number of steps returns to
+// that buffer, so such a graph, and even numbers of steps between its replays,
+// continue the run.  From the first capture on, the handle keeps this for
+// launches of several steps too: lbm_step splits one launch in two where the
+// launches and the steps differ in parity.
+bool keep_parity(lbm_ctx* h)
+{
+    if (launch_steps_max(h) == 1) return false;  // every step flips
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &c) != hipSuccess) {
+        (void)hipGetLastError();  // the null stream beside another stream's capture
+        return h->keep_parity;
+    }
+    if (c == hipStreamCaptureStatusActive) h->keep_parity = true;
+    return h->keep_parity;
+}
+
 // Where the current state is, and in which layout (StateLayout).
 void state_view(const lbm_ctx* h, const void** state, int* layout)
 {
@@ -1091,10 +1110,11 @@ lbm_status lbm_step(lbm_t h, int64_t n)
         if (!one_buffer(h))
             if (lbm_status st = ensure_second(h)) return st;
         if (lbm_status st = build_tables(h)) return st;
+        const bool keep = keep_parity(h);
         const int G = graph_steps(h);
         int64_t left = n;
-        if (G > 1) {
-            while (left >= G) {
+        if (G > 1 && !(keep && ((launches_for(h, G) ^ G) & 1))) {
+            while (left >= (keep ? h->graph_chunk : G)) {
                 if (lbm_status st = build_graph(h, h->cur)) return st;
                 HIP_TRY(hipGraphLaunch(h->gexec[h->cur], h->stream), "hipGraphLaunch");
                 h->cur ^= int(launches_for(h, G) & 1);
@@ -1102,8 +1122,16 @@ lbm_status lbm_step(lbm_t h, int64_t n)
                 left -= G;
             }
         }
+        bool split = keep && ((launches_for(h, left) ^ left) & 1);
+        int rest = 0;  // of a split launch
         while (left > 0) {
-            const int k = steps_in_launch(h, left);
+            int k = rest > 0 ? rest : steps_in_launch(h, left);
+            rest = 0;
+            if (split && k > 1) {
+                rest = k - 1;
+                k = 1;
+                split = false;
+            }
             hipError_t e = launch_steps(h, h->cur, k, h->stream);
             if (e != hipSuccess) return fail_hip(e, "step kernel launch");
             h->cur ^= 1;
