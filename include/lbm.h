@@ -185,8 +185,9 @@ lbm_status lbm_init(lbm_t h, const double* rho, const double* u, int32_t on_devi
  * (periodic), collide, store.  Asynchronous on the handle's stream; long runs
  * are issued as captured graphs of graph_chunk steps.  LBM_ESTATE before init.
  * An even number of steps that the caller captures on that stream may be
- * replayed, with even numbers of steps between the replays; t counts the
- * captured call once. */
+ * replayed, with even numbers of steps between the replays; captured at an even
+ * number of steps since lbm_init or lbm_set_state, also after a later call of
+ * these.  t counts the captured call once. */
 lbm_status lbm_step(lbm_t h, int64_t n);
 
 /* Build (or rebuild) the captured step graphs now, so that a later lbm_step

@@ -146,7 +146,8 @@ struct lbm_ctx {
     int* d_box_chunk_begin = nullptr;
     double* d_partial = nullptr;
     double* d_out = nullptr;
-    bool keep_parity = false;       // a caller captured steps (keep_parity below)
+    int phase = 0;                  // parity of the steps since the state was last set
+    bool keep_parity = false;       // a caller captured this handle's work (capturing below)
     // captured step graphs, one per starting buffer
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gexec_steps[2] = {0, 0};
@@ -721,22 +722,34 @@ int graph_steps(const lbm_ctx* h)
     return (tiled(h) && h->graph_chunk > m) ? h->graph_chunk - h->graph_chunk % m : h->graph_chunk;
 }
 
-// A graph that the caller captures from lbm_step replays from the buffer that
-// was current then.  With one step per launch an even number of steps returns to
-// that buffer, so such a graph, and even numbers of steps between its replays,
-// continue the run.  From the first capture on, the handle keeps this for
-// launches of several steps too: lbm_step splits one launch in two where the
-// launches and the steps differ in parity.
-bool keep_parity(lbm_ctx* h)
+// Whether the caller is capturing the handle's stream.
+// A graph that the caller captures reads and writes the buffers that were in
+// use then.  With one step per launch the state is in buf[0] at every even
+// number of steps since it was set (lbm_init, lbm_set_state, a kernel change),
+// so such a graph continues the run after an even number of further steps, and
+// starts anew after new fields.  With several steps per launch the buffers
+// follow the launches instead.  The first capture that is seen therefore names
+// the buffers anew, so that cur is the phase, and lbm_step keeps it so from then
+// on: it splits one launch in two where the launches and the steps differ in
+// parity.
+bool capturing(lbm_ctx* h)
 {
-    if (launch_steps_max(h) == 1) return false;  // every step flips
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(h->stream, &c) != hipSuccess) {
         (void)hipGetLastError();  // the null stream beside another stream's capture
-        return h->keep_parity;
+        return false;
     }
-    if (c == hipStreamCaptureStatusActive) h->keep_parity = true;
-    return h->keep_parity;
+    if (c != hipStreamCaptureStatusActive) return false;
+    if (!h->keep_parity) {
+        h->keep_parity = true;
+        if (!one_buffer(h) && h->cur != h->phase) {
+            std::swap(h->buf[0], h->buf[1]);
+            std::swap(h->gexec[0], h->gexec[1]);
+            std::swap(h->gexec_steps[0], h->gexec_steps[1]);
+            h->cur = h->phase;
+        }
+    }
+    return true;
 }
 
 // Where the current state is, and in which layout (StateLayout).
@@ -755,7 +768,10 @@ lbm_status canonicalize(lbm_ctx* h)
 {
     if (!h->initialized) return LBM_OK;
     const int layout = state_layout(h);
-    if (layout == kNatural && (one_buffer(h) || h->cur == 0)) return LBM_OK;
+    if (layout == kNatural && (one_buffer(h) || h->cur == 0)) {
+        h->phase = 0;
+        return LBM_OK;
+    }
     if (layout != kNatural) {
         if (lbm_status st = ensure_second(h)) return st;
         const int block = effective_block(h);
@@ -764,7 +780,7 @@ lbm_status canonicalize(lbm_ctx* h)
         if (e != hipSuccess) return fail_hip(e, "relayout kernel");
     }
     std::swap(h->buf[0], h->buf[1]);
-    h->cur = 0;
+    h->cur = h->phase = 0;
     // the natural state at cur = 0 is the scalar step's starting point, not
     // the twist step's; callers choose the next kernel right after
     if (twisted(h)) h->kernel = LBM_KERNEL_SCALAR;
@@ -794,7 +810,7 @@ lbm_status enter_kernel_layout(lbm_ctx* h)
                                    single_geom(h, block), block, h->stream);
     if (e != hipSuccess) return fail_hip(e, "relayout kernel");
     std::swap(h->buf[0], h->buf[1]);
-    h->cur = 0;
+    h->cur = h->phase = 0;
     drop_graphs(h);
     return LBM_OK;
 }
@@ -1070,7 +1086,7 @@ lbm_status lbm_init(lbm_t h, const double* rho, const double* u, int32_t on_devi
         if (t2) (void)hipFree(du);
         if (e != hipSuccess) return fail_hip(e, "init kernel");
         if (e2 != hipSuccess) return fail_hip(e2, "init synchronize");
-        h->cur = 0;
+        h->cur = h->phase = 0;
         h->t = 0;
         h->initialized = true;
         return LBM_OK;
@@ -1110,7 +1126,8 @@ lbm_status lbm_step(lbm_t h, int64_t n)
         if (!one_buffer(h))
             if (lbm_status st = ensure_second(h)) return st;
         if (lbm_status st = build_tables(h)) return st;
-        const bool keep = keep_parity(h);
+        (void)capturing(h);
+        const bool keep = h->keep_parity && launch_steps_max(h) > 1;
         const int G = graph_steps(h);
         int64_t left = n;
         if (G > 1 && !(keep && ((launches_for(h, G) ^ G) & 1))) {
@@ -1118,6 +1135,7 @@ lbm_status lbm_step(lbm_t h, int64_t n)
                 if (lbm_status st = build_graph(h, h->cur)) return st;
                 HIP_TRY(hipGraphLaunch(h->gexec[h->cur], h->stream), "hipGraphLaunch");
                 h->cur ^= int(launches_for(h, G) & 1);
+                h->phase ^= G & 1;
                 h->t += G;
                 left -= G;
             }
@@ -1135,6 +1153,7 @@ lbm_status lbm_step(lbm_t h, int64_t n)
             hipError_t e = launch_steps(h, h->cur, k, h->stream);
             if (e != hipSuccess) return fail_hip(e, "step kernel launch");
             h->cur ^= 1;
+            h->phase ^= k & 1;
             h->t += k;
             left -= k;
         }
@@ -1287,6 +1306,7 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
         // the scalar step at cur = 0 (the twist step's even layout is not)
         h->kernel = LBM_KERNEL_SCALAR;
         h->cur = cur0;
+        h->phase = 0;
         h->t = t0;
         h->graph_chunk = chunk0;
         if (st != LBM_OK) {
@@ -1539,7 +1559,7 @@ lbm_status lbm_set_state(lbm_t h, const void* buf, size_t bytes)
         }
         HIP_TRY(hipMemcpyAsync(h->buf[0], src, payload, hipMemcpyHostToDevice, h->stream), "copy state to device");
         HIP_TRY(hipStreamSynchronize(h->stream), "set_state synchronize");
-        h->cur = 0;
+        h->cur = h->phase = 0;
         h->t = hd.t;
         h->initialized = true;
         return LBM_OK;
