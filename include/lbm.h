@@ -289,7 +289,9 @@ lbm_status lbm_residual(lbm_t h, const double* rho_ref, const double* u_ref, int
  * each GPU until the process ends, so a handle of at most 65536 reduction
  * chunks of 4096 sites is accepted (2^28 sites in one box); larger handles get
  * LBM_EINVAL.  All calls on one GPU share that array: calls that overlap on
- * one GPU (two streams, two threads) race and give wrong results. */
+ * one GPU (two streams, two threads) race and give wrong results.  A captured
+ * call may be replayed after even numbers of further steps, and after lbm_init
+ * or lbm_set_state if it was captured at an even number of steps since. */
 lbm_status lbm_residual_noalloc(lbm_t h, const double* rho_ref, const double* u_ref, double* out);
 
 /* Checkpoint: bytes needed by lbm_get_state (a header plus the raw stored

@@ -1441,6 +1441,7 @@ lbm_status lbm_residual_noalloc(lbm_t h, const double* rho_ref, const double* u_
         HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
         double* partial = nullptr;
         if (lbm_status st = scratch_address(h->device, &partial)) return st;
+        (void)capturing(h);  // a captured reader, too, is bound to the current buffer
         const void* state = nullptr;
         int layout = kNatural;
         state_view(h, &state, &layout);

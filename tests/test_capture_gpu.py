@@ -95,3 +95,34 @@ def test_new_fields_after_a_capture(kernel, dims, warm):
         g.replay()
         b.step(2)
         assert _same(a, b)
+
+
+@pytest.mark.parametrize("warm", [2, 8])
+@pytest.mark.parametrize("kernel,dims", BOXES)
+def test_captured_reader(kernel, dims, warm):
+    """A captured lbm_residual_noalloc reports the current state after even
+    numbers of eager steps and after new fields."""
+    import torch
+    from paper_2002_02503_amd import lbm
+
+    tau, rho, u = _state(dims, 3)
+    _, rho2, u2 = _state(dims, 4)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), \
+            lbm.Simulation("D3Q19", dims, tau, dtype="fp32", kernel=kernel, stream=s) as a:
+        dr, du = torch.from_numpy(rho).cuda(), torch.from_numpy(u).cuda()
+        out, ref = torch.zeros(4, dtype=torch.float64, device="cuda"), torch.zeros(4, dtype=torch.float64, device="cuda")
+        a.init(rho, u).step(warm)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            a.residual_noalloc(dr, du, out)
+        for eager in (2, 2, 8, 34):
+            a.step(eager)
+            g.replay()
+            a.residual_noalloc(dr, du, ref)
+            assert torch.equal(out, ref) and float(ref[0]) > 0.0
+        a.init(rho2, u2).step(4)
+        g.replay()
+        a.residual_noalloc(dr, du, ref)
+        assert torch.equal(out, ref)
