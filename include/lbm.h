@@ -183,7 +183,8 @@ lbm_status lbm_init(lbm_t h, const double* rho, const double* u, int32_t on_devi
 
 /* Advance n >= 0 steps of eq. lbe-reg: per site pull f_i from x - c_i
  * (periodic), collide, store.  Asynchronous on the handle's stream; long runs
- * are issued as captured graphs of graph_chunk steps.  LBM_ESTATE before init.
+ * are issued as captured graphs of graph_chunk steps, or as direct launches
+ * while the caller captures the stream.  LBM_ESTATE before init.
  * An even number of steps that the caller captures on that stream may be
  * replayed, with even numbers of steps between the replays; captured at an even
  * number of steps since lbm_init or lbm_set_state, also after a later call of

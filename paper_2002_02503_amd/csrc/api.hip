@@ -1126,12 +1126,14 @@ lbm_status lbm_step(lbm_t h, int64_t n)
         if (!one_buffer(h))
             if (lbm_status st = ensure_second(h)) return st;
         if (lbm_status st = build_tables(h)) return st;
-        (void)capturing(h);
+        // a caller's capture records kernels: an executable graph launched into
+        // it would not become part of it
+        const bool record = capturing(h);
         const bool keep = h->keep_parity && launch_steps_max(h) > 1;
         const int G = graph_steps(h);
         int64_t left = n;
-        if (G > 1 && !(keep && ((launches_for(h, G) ^ G) & 1))) {
-            while (left >= (keep ? h->graph_chunk : G)) {
+        if (G > 1 && !record && !(keep && ((launches_for(h, G) ^ G) & 1))) {
+            while (left >= G) {
                 if (lbm_status st = build_graph(h, h->cur)) return st;
                 HIP_TRY(hipGraphLaunch(h->gexec[h->cur], h->stream), "hipGraphLaunch");
                 h->cur ^= int(launches_for(h, G) & 1);

@@ -126,3 +126,33 @@ def test_captured_reader(kernel, dims, warm):
         g.replay()
         a.residual_noalloc(dr, du, ref)
         assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("chunk,n", [(None, 32), (None, 64), (None, 70), (4, 8), (4, 10), (2, 6)])
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("kernel,dims", BOXES)
+def test_captured_steps_of_a_graph_chunk_and_more(kernel, dims, prepared, chunk, n):
+    """Captured counts at and above the handle's own graph chunk, whose graphs
+    exist (prepared) or not."""
+    import torch
+    from paper_2002_02503_amd import lbm
+
+    tau, rho, u = _state(dims, 5)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), \
+            lbm.Simulation("D3Q19", dims, tau, dtype="fp32", kernel=kernel, stream=s, graph_chunk=chunk) as a, \
+            lbm.Simulation("D3Q19", dims, tau, dtype="fp32", kernel="scalar", graph_chunk=1, stream=s) as b:
+        a.init(rho, u).step(2)
+        b.init(rho, u).step(2)
+        if prepared:
+            a.prepare()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            a.step(n)
+        for eager in (0, 2, 40):
+            g.replay()
+            b.step(n)
+            assert _same(a, b)
+            a.step(eager)
+            b.step(eager)
+            assert _same(a, b)
