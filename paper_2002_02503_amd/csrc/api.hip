@@ -1270,6 +1270,10 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
         // timed window would charge its capture to one candidate
         const int chunk0 = h->graph_chunk;
         h->graph_chunk = 1;
+        // nor are launches split for an earlier capture of the caller's while
+        // they are timed (capturing); the state is set anew afterwards
+        const bool keep0 = h->keep_parity;
+        h->keep_parity = false;
         hipEvent_t e0 = nullptr, e1 = nullptr;
         hipError_t e = hipMemcpyAsync(saved, h->buf[cur0], h->state_bytes, hipMemcpyDeviceToDevice, h->stream);
         if (e == hipSuccess) e = hipEventCreate(&e0);
@@ -1311,6 +1315,7 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
         h->phase = 0;
         h->t = t0;
         h->graph_chunk = chunk0;
+        h->keep_parity = keep0;
         if (st != LBM_OK) {
             (void)apply_choice(h, old);
             return st;
