@@ -122,15 +122,19 @@ static int even_piece(int64_t n, int64_t most)
     return int((n + pieces - 1) / pieces);
 }
 
+// Widest x-piece of a column: at most 128 sites, and at least two rows with
+// their ring in the block's threads.
+static int widest_piece(int threads) { return std::min(128, threads / 4 - 2); }
+
 void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
 {
-    *tx = (nx % kTwoStepTileX == 0) ? kTwoStepTileX : even_piece(nx, 128);
+    *tx = (nx % kTwoStepTileX == 0) ? kTwoStepTileX : even_piece(nx, widest_piece(two_step_threads(elem)));
     *ty = even_piece(ny, two_step_threads(elem) / (*tx + 2) - 2);
 }
 
 void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
 {
-    *tx = even_piece(nx, 128);
+    *tx = even_piece(nx, widest_piece(batch_columns_threads(elem)));
     const int64_t most = std::min<int64_t>(ny, batch_columns_threads(elem) / (*tx + 2) - 2);
     int64_t best = 0;
     for (int64_t t = most; t >= 1; --t) {

@@ -76,11 +76,14 @@ bool columns_fit(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
 // Column tile of the two-step kernel for a box: 64 x two_step_tile_y where nx
 // is a multiple of 64; else x in even pieces of at most 128, since rows that
 // do not start on a cache line pay for partly used lines at both ends of a
-// piece, and as many rows as the block's threads hold.  Measured, us per step
-// (tile): D3Q19 FP32 201 x 150 x 77 54 (101 x 4), 62 (67 x 8), 71 (51 x 11);
+// piece, and as many rows as the block's threads hold.  A piece leaves room for
+// two rows at least (110 sites at most in FP64, where 111 to 128 left one):
+// step 1 takes three sites for each site of a single row, two for two.
+// Measured, us per step (tile): D3Q19 FP32 201 x 150 x 77 54 (101 x 4), 62 (67 x 8), 71 (51 x 11);
 // 100^3 21 (100 x 4), 29 (50 x 10), 33 (34 x 17); 255^3 363 (128 x 3), 411 (64 x
 // 8); 160^3 83 (80 x 6 and 160 x 2), 93 (32 x 18); FP64 100^3 38 (100 x 2), 44
-// (50 x 6).
+// (50 x 6), 120^3 69 (60 x 5), 84 (120 x 1), 240^3 589 (80 x 3), 912 (120 x 1;
+// one-site step 706), 255^3 542 (85 x 3), 689 (128 x 1).
 void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 
 // Rounds of a compute unit's four SIMDs that a plane of a column tile takes:
@@ -88,8 +91,9 @@ void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 constexpr int column_rounds1(int tx, int ty) { return ((tx + 2) * (ty + 2) + 255) / 256; }
 constexpr int column_rounds(int tx, int ty) { return column_rounds1(tx, ty) + (tx * ty + 255) / 256; }
 
-// Column tile of the batched two-step kernel: x in even pieces of at most 128,
-// and the rows that take the fewest rounds over the box, since the busiest
+// Column tile of the batched two-step kernel: x in even pieces of at most 128
+// (126 in FP64, for two rows: 30 boxes of 128 x 128 x 8 173 us per step, 227 with
+// one), and the rows that take the fewest rounds over the box, since the busiest
 // SIMD sets the time of a plane.
 void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 

@@ -115,3 +115,19 @@ def test_batched_columns_choice():
     with pytest.raises(lbm.LBMError) as e:
         lbm.Simulation("D3Q39", [(8, 8, 8), (9, 9, 9)], [0.6, 0.7], kernel="columns", torch_memory=False)
     assert e.value.name == "LBM_EINVAL"
+
+
+@pytest.mark.parametrize("dims", [(110, 7, 5), (111, 7, 5), (120, 9, 4), (128, 1, 6), (223, 5, 3), (255, 3, 4)])
+def test_fp64_columns_at_the_widest_piece(dims):
+    """Rows on both sides of the widest FP64 piece (110 sites) and a single row."""
+    rho, u = _fields(dims, seed=sum(dims))
+    a = run_gpu("D3Q19", dims, 0.6, "fp64", rho, u, 9, kernel="columns")
+    b = run_gpu("D3Q19", dims, 0.6, "fp64", rho, u, 9, kernel="scalar")
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+def test_fp64_batched_columns_at_the_widest_piece():
+    dims = [(126, 6, 4), (127, 6, 4), (128, 1, 3), (128, 9, 5), (253, 4, 3)]
+    a = _batch("D3Q19", dims, [0.6] * len(dims), "fp64", 7, (4, 3), "columns")
+    b = _batch("D3Q19", dims, [0.6] * len(dims), "fp64", 7, (4, 3), "scalar")
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
