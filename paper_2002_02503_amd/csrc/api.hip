@@ -78,8 +78,6 @@ constexpr int64_t kTwoStepSites = 64 * 64 * 64;
 constexpr int64_t kColumnsSites = 400000;
 constexpr int64_t kColumnsSites16 = 2000000;  // D3Q19 in 16-bit storage
 constexpr int64_t kColumnsRows = 64;          // x-rows
-constexpr int64_t kBatchColumnsSites = 700000;
-constexpr int64_t kBatchColumnsMean = 24 * 24 * 24;
 // Runs of the batched two-step kernel (step2_batch.hpp).
 constexpr int kRunPlanes = 16;
 constexpr int kMaxRounds = 12;
@@ -134,7 +132,8 @@ struct lbm_ctx {
     TileDesc* d_tiles = nullptr;
     int ntiles = 0;
     BoxDesc* d_boxes = nullptr;
-    // batched two-step tables
+    // batched two-step kernel: the default where no launch shape is set; its tables
+    bool columns_pay = false;
     ColumnDesc* d_columns = nullptr;
     ColumnStart* d_starts = nullptr;
     int column_rounds = 0;
@@ -216,23 +215,12 @@ int auto_kernel(const lbm_ctx* h)
     return (pays && columns_ok(h)) ? LBM_KERNEL_COLUMNS : LBM_KERNEL_SCALAR;
 }
 
-// The batched two-step kernel is the default for FP32 and FP64 batches large
-// enough in all and box by box (the two rows and planes around a column cost
-// small boxes more).  D3Q19, us per step, one-step against two-step: 256 boxes of
-// sides 16-64 FP32 449 / 351 and FP64 900 / 660, 24-40 212 / 183, 16-32 93 / 89, 8-24
-// 31 / 43; 16 boxes of 16-64 (820,000 sites) 24 / 20; 16-bit storage is bound by
-// instruction issue (256 boxes of 32-64 BF16 369 / 496).
-bool batch_columns_pay(const lbm_ctx* h)
-{
-    return h->block == 0 && h->grid == 0 && h->elem >= 4 && h->nsites >= kBatchColumnsSites &&
-           h->nsites >= kBatchColumnsMean * h->nbox && columns_ok(h);
-}
-
 int effective_kernel(const lbm_ctx* h)
 {
     if (!is_single(h)) {
         if (h->kernel != LBM_KERNEL_AUTO) return h->kernel;
-        return batch_columns_pay(h) ? LBM_KERNEL_COLUMNS : LBM_KERNEL_SCALAR;
+        const bool columns = h->columns_pay && h->block == 0 && h->grid == 0;
+        return columns ? LBM_KERNEL_COLUMNS : LBM_KERNEL_SCALAR;
     }
     return h->kernel == LBM_KERNEL_AUTO ? auto_kernel(h) : h->kernel;
 }
@@ -532,6 +520,7 @@ lbm_status create_common(lbm_t* out, int32_t lattice, int32_t nbox, const int64_
                 hipSuccess)
                 return cleanup(fail_hip(e, "copy boxes"));
         }
+        h->columns_pay = nbox > 1 && batch_columns_pay(L, dtype, nbox, dims);
         if (nbox == 1 && !tile_plan(L, dtype, dims[0], dims[1], dims[2], h->cus, &h->tile)) h->tile = TilePlan{};
         *out = h;
         return LBM_OK;

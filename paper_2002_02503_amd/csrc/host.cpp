@@ -147,6 +147,29 @@ void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
     }
 }
 
+bool batch_columns_pay(const LatticeInfo& L, int dtype, int nbox, const int64_t* dims)
+{
+    const int64_t elem = int64_t(storage_bytes(dtype));
+    if (elem < 4) return false;
+    int64_t sites = 0;
+    for (int b = 0; b < nbox; ++b) {
+        const int64_t* d = dims + 3 * b;
+        if (!columns_fit(L, dtype, d[0], d[1], d[2])) return false;
+        sites += d[0] * d[1] * d[2];
+    }
+    if (sites < kBatchColumnsSites || sites < kBatchColumnsMean * nbox) return false;
+    int64_t rounds = 0;
+    for (int b = 0; b < nbox; ++b) {
+        const int64_t nx = dims[3 * b], ny = dims[3 * b + 1], nz = dims[3 * b + 2];
+        int tx = 0, ty = 0;
+        batch_column_tile(size_t(elem), nx, ny, &tx, &ty);
+        const int64_t r = std::max(column_rounds(tx, ty), elem == 4 ? 4 : 0);
+        rounds += ((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * (nz * r + 2 * column_rounds1(tx, ty));
+    }
+    // 256 sites a round against two steps of every site
+    return 10 * 256 * rounds <= (elem == 4 ? 18 : 20) * 2 * sites;
+}
+
 int64_t tile_region(const LatticeInfo& L, const TilePlan& p, int64_t nx, int steps)
 {
     const int64_t g = 2 * (steps - 1);

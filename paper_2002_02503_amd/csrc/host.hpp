@@ -97,6 +97,25 @@ constexpr int column_rounds(int tx, int ty) { return column_rounds1(tx, ty) + (t
 // SIMD sets the time of a plane.
 void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 
+// Whether the default for a batch is the two-step kernel: FP32 and FP64 batches
+// large enough in all and box by box, whose planes fill the blocks and whose
+// columns are not all ring.  D3Q19, us per step, one-step against two-step: 256
+// boxes of sides 16-64 FP32 437 / 347 and FP64 778 / 581, 24-40 215 / 181, 16-32 93 /
+// 89, 8-24 31 / 43; 16 boxes of 16-64 (820,000 sites) 24 / 20; 16-bit storage is
+// bound by instruction issue (256 boxes of 32-64 BF16 369 / 496).
+// The shapes go by the rounds that the columns take over two steps, ring and the
+// two extra step-1 planes of a column included, against the two rounds of 256
+// sites: up to 1.8 times as many in FP32, where a plane counts four rounds at
+// least (fewer lanes leave its latency open), up to 2 in FP64.  One-step against
+// two-step, (times as many): FP32 boxes of 48^3 177 / 119 (1.36), 100 x 100 x 10
+// 101 / 92 (1.79), 300 x 300 x 8 147 / 153 (1.84), 16 x 16 x 400 153 / 161 (2.0),
+// 1000 x 1000 x 1 201 / 433 (3.8), 4 x 4 x 5000 120 / 1136 (32); FP64 24^3 180 / 121
+// (1.85), 200 x 200 x 6 196 / 182 (2.0), 20000 x 4 x 4 665 / 897 (2.05), 4 x 4 x 5000
+// 251 / 1206 (16).
+constexpr int64_t kBatchColumnsSites = 700000;
+constexpr int64_t kBatchColumnsMean = 24 * 24 * 24;
+bool batch_columns_pay(const LatticeInfo& L, int dtype, int nbox, const int64_t* dims);
+
 constexpr int kTileMaxSteps = 16;
 constexpr int64_t kTileMaxLds = 160 * 1024;  // a compute unit's LDS
 

@@ -1,9 +1,10 @@
 // Check the plans that the multi-step kernels are launched with
 // (paper_2002_02503_amd/csrc/host.cpp), which the kernels rely on unchecked, for
-// tests/test_host_plans.py: column tiles over all row lengths.  A failed
-// expectation exits 2.
+// tests/test_host_plans.py: column tiles over all row lengths, and the shapes for
+// which a default is taken.  A failed expectation exits 2.
 #include <cstdint>
 #include <cstdio>
+#include <vector>
 
 #include "host.hpp"
 
@@ -52,9 +53,44 @@ static void test_column_tiles()
     }
 }
 
+// n equal boxes
+static bool batch_pays(int lat, int dtype, int n, int64_t nx, int64_t ny, int64_t nz, std::vector<int64_t> more = {})
+{
+    LatticeInfo L;
+    lattice_info(lat, &L);
+    for (int k = 0; k < n; ++k) more.insert(more.end(), {nx, ny, nz});
+    return batch_columns_pay(L, dtype, int(more.size() / 3), more.data());
+}
+
+static void test_batch_rule()
+{
+    // lattice codes: 0 D2Q9, 1 D3Q19, 2 D3Q39, 3 D3Q15; dtype codes: 0 FP64 .. 3 BF16
+    for (int lat : {1, 3}) {
+        for (int dtype : {0, 1}) {
+            for (int64_t a : {24, 32, 40, 48, 64, 96}) EXPECT(batch_pays(lat, dtype, 64, a, a, a), "%ld", long(a));
+            EXPECT(!batch_pays(lat, dtype, 8, 20, 20, 20), "few sites");
+            EXPECT(!batch_pays(lat, dtype, 200, 20, 20, 20), "small boxes");
+            // one layer, few rows, narrow: mostly ring, or few lanes
+            EXPECT(!batch_pays(lat, dtype, 8, 1000, 1000, 1), "a layer");
+            EXPECT(!batch_pays(lat, dtype, 8, 1000, 1000, 2), "two layers");
+            EXPECT(!batch_pays(lat, dtype, 8, 1000, 1, 1000), "one row");
+            EXPECT(!batch_pays(lat, dtype, 40, 20000, 2, 2), "few rows");
+            EXPECT(!batch_pays(lat, dtype, 60, 4, 4, 5000), "narrow");
+            EXPECT(!batch_pays(lat, dtype, 60, 8, 8, 2000), "narrow");
+            EXPECT(!batch_pays(lat, dtype, 8, 40, 40, 40, {2000, 2000, 1}), "one layer among boxes");
+            EXPECT(batch_pays(lat, dtype, 64, 40, 40, 40, {40, 40, 1, 5, 5, 400}), "a small share of thin boxes");
+        }
+        EXPECT(!batch_pays(lat, 2, 64, 40, 40, 40) && !batch_pays(lat, 3, 64, 40, 40, 40), "16-bit");
+    }
+    EXPECT(!batch_pays(0, 1, 64, 1000, 1000, 1) && !batch_pays(2, 1, 64, 40, 40, 40), "no column kernel");
+    const int64_t wide = (int64_t(1) << 21);
+    EXPECT(!batch_pays(1, 1, 2, wide, 2, 2), "rows at the limit");
+}
+
 int main()
 {
     test_column_tiles();
+    test_batch_rule();
     if (g_fail) return 2;
     std::printf("host plan driver: ok\n");
     return 0;

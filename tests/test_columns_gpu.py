@@ -131,3 +131,17 @@ def test_fp64_batched_columns_at_the_widest_piece():
     a = _batch("D3Q19", dims, [0.6] * len(dims), "fp64", 7, (4, 3), "columns")
     b = _batch("D3Q19", dims, [0.6] * len(dims), "fp64", 7, (4, 3), "scalar")
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+def test_batched_columns_choice_by_shape():
+    """Batches whose columns are mostly ring, or too narrow to fill a block, keep
+    the one-step kernel."""
+    from paper_2002_02503_amd import lbm
+
+    names = {v: k for k, v in lbm.KERNELS.items()}
+    for dims, want in [([(1000, 1000, 1)] * 8, "scalar"), ([(4, 4, 5000)] * 60, "scalar"),
+                       ([(20000, 2, 2)] * 40, "scalar"), ([(48, 48, 48)] * 64, "columns"),
+                       ([(300, 300, 16)] * 8, "columns")]:
+        for dtype in ("fp32", "fp64"):
+            with lbm.Simulation("D3Q19", dims, [0.7] * len(dims), dtype=dtype, torch_memory=False) as sim:
+                assert names[sim.info()["kernel"]] == want, (dims[0], dtype)
