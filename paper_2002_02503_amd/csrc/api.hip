@@ -73,11 +73,6 @@ constexpr int kTuneRounds = 3;
 constexpr size_t kCachedStoresFrom = size_t(40) << 20;
 constexpr size_t kCachedStoresTo = size_t(128) << 20;
 
-// Smallest boxes for which the default takes the two-step kernel (auto_kernel).
-constexpr int64_t kTwoStepSites = 64 * 64 * 64;
-constexpr int64_t kColumnsSites = 400000;
-constexpr int64_t kColumnsSites16 = 2000000;  // D3Q19 in 16-bit storage
-constexpr int64_t kColumnsRows = 64;          // x-rows
 // Runs of the batched two-step kernel (step2_batch.hpp).
 constexpr int kRunPlanes = 16;
 constexpr int kMaxRounds = 12;
@@ -132,8 +127,8 @@ struct lbm_ctx {
     TileDesc* d_tiles = nullptr;
     int ntiles = 0;
     BoxDesc* d_boxes = nullptr;
-    // batched two-step kernel: the default where no launch shape is set; its tables
-    bool columns_pay = false;
+    bool columns_pay = false;       // the two-step kernel gains on this machine or batch
+    // batched two-step tables
     ColumnDesc* d_columns = nullptr;
     ColumnStart* d_starts = nullptr;
     int column_rounds = 0;
@@ -189,38 +184,23 @@ bool columns_ok(const lbm_ctx* h)
 // The tile kernel has a plan for this box.
 bool tile_ok(const lbm_ctx* h) { return is_single(h) && h->tile.steps > 0; }
 
-// Without a choice by the caller or the tuner: the tile kernel where it has a
-// plan; the two-step kernel on larger boxes (in 16-bit storage only where rows
-// are not whole cache lines); else the one-site step, also where the caller set
-// a launch shape, which is that step's.
-// Two-step against one-site, us per step of D3Q19 FP32: tiles of 64 columns 64^3
-// 7.3 / 8.5, 128^3 36 / 53, 256^3 248 / 422; other tiles 65^3 12.0 / 12.0,
-// 80^3 13 / 17, 100^3 17.4 / 35, 201 x 150 x 77 54 / 76, 255^3 363 / 646, FP64 100^3
-// 38 / 59.  In 16-bit storage on rows of 64 columns both are bound by instruction
-// issue and nothing is gained (FP16 128^3 26.4 / 26, 256^3 209 / 206); on others
-// D3Q19 needs more sites (BF16 101^3 26 / 24, 130^3 43 / 50, FP16 201 x 150 x 77 41 /
-// 48) and D3Q15 does not gain (BF16 130^3 39 / 35).  A box of one layer or of few
-// rows computes the ring for nothing: 1024 x 1024 x 1 37 / 28, 1000 x 1 x 1000 36 /
-// 32, 100000 x 2 x 2 18 / 13, but 512 x 512 x 2 13.9 / 15.6 and 1000 x 2 x 500 24 / 32.
+// Without a choice by the caller or the tuner: the one-site step where the
+// caller set a launch shape, which is that step's; else the tile kernel where it
+// has a plan, the two-step kernel where it gains (host.hpp, columns_pay), or the
+// one-site step.
 int auto_kernel(const lbm_ctx* h)
 {
     if (h->block > 0 || h->grid > 0) return LBM_KERNEL_SCALAR;
     if (tile_ok(h)) return LBM_KERNEL_TILE;
-    const int64_t ny = h->dims[1], nz = h->dims[2];
-    if (ny < 2 || nz < 2 || ny * nz < kColumnsRows) return LBM_KERNEL_SCALAR;
-    if (two_step_ok(h))
-        return (h->elem >= 4 && h->nsites >= kTwoStepSites) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_SCALAR;
-    const bool pays = h->elem >= 4 ? h->nsites >= kColumnsSites
-                                   : h->lattice == LBM_D3Q19 && h->nsites >= kColumnsSites16;
-    return (pays && columns_ok(h)) ? LBM_KERNEL_COLUMNS : LBM_KERNEL_SCALAR;
+    if (!h->columns_pay) return LBM_KERNEL_SCALAR;
+    return two_step_ok(h) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_COLUMNS;
 }
 
 int effective_kernel(const lbm_ctx* h)
 {
     if (!is_single(h)) {
         if (h->kernel != LBM_KERNEL_AUTO) return h->kernel;
-        const bool columns = h->columns_pay && h->block == 0 && h->grid == 0;
-        return columns ? LBM_KERNEL_COLUMNS : LBM_KERNEL_SCALAR;
+        return (h->columns_pay && h->block == 0 && h->grid == 0) ? LBM_KERNEL_COLUMNS : LBM_KERNEL_SCALAR;
     }
     return h->kernel == LBM_KERNEL_AUTO ? auto_kernel(h) : h->kernel;
 }
@@ -520,7 +500,8 @@ lbm_status create_common(lbm_t* out, int32_t lattice, int32_t nbox, const int64_
                 hipSuccess)
                 return cleanup(fail_hip(e, "copy boxes"));
         }
-        h->columns_pay = nbox > 1 && batch_columns_pay(L, dtype, nbox, dims);
+        h->columns_pay = nbox == 1 ? columns_pay(L, dtype, dims[0], dims[1], dims[2])
+                                   : batch_columns_pay(L, dtype, nbox, dims);
         if (nbox == 1 && !tile_plan(L, dtype, dims[0], dims[1], dims[2], h->cus, &h->tile)) h->tile = TilePlan{};
         *out = h;
         return LBM_OK;

@@ -147,6 +147,16 @@ void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
     }
 }
 
+bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz)
+{
+    const int64_t elem = int64_t(storage_bytes(dtype));
+    if (!columns_fit(L, dtype, nx, ny, nz) || nx > kMaxSites / ny / nz) return false;
+    if (ny < 2 || nz < 2 || ny * nz < kColumnsRows) return false;
+    const int64_t sites = nx * ny * nz;
+    if (elem == 2) return L.Q == 19 && nx % kTwoStepTileX != 0 && sites >= kColumnsSites16;
+    return sites >= (two_step_fits(L, dtype, nx, ny, nz) ? kTwoStepSites : kColumnsSites);
+}
+
 bool batch_columns_pay(const LatticeInfo& L, int dtype, int nbox, const int64_t* dims)
 {
     const int64_t elem = int64_t(storage_bytes(dtype));

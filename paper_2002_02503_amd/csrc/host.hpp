@@ -97,6 +97,25 @@ constexpr int column_rounds(int tx, int ty) { return column_rounds1(tx, ty) + (t
 // SIMD sets the time of a plane.
 void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 
+// Whether the default for a single box is the two-step kernel, rather than the
+// one-site step: large boxes, in 16-bit storage only where rows are not whole
+// cache lines.
+// Two-step against one-site, us per step of D3Q19 FP32: tiles of 64 columns 64^3
+// 7.3 / 8.5, 128^3 36 / 53, 256^3 248 / 422; other tiles 65^3 12.0 / 12.0,
+// 80^3 13 / 17, 100^3 17.4 / 35, 201 x 150 x 77 54 / 76, 255^3 363 / 646, FP64 100^3
+// 38 / 59.  In 16-bit storage on rows of whole lines both are bound by instruction
+// issue and nothing is gained (FP16 128^3 26.4 / 26, 256^3 209 / 206; also where ny
+// is no multiple of the tile: BF16 128 x 130 x 130 36 / 30); on others D3Q19 needs
+// more sites (BF16 101^3 26 / 24, 130^3 43 / 50, FP16 201 x 150 x 77 41 / 48) and D3Q15
+// does not gain (BF16 130^3 39 / 35).  A box of one layer or of few rows computes
+// the ring for nothing: 1024 x 1024 x 1 37 / 28, 1000 x 1 x 1000 36 / 32, 100000 x 2 x 2
+// 18 / 13, but 512 x 512 x 2 13.9 / 15.6 and 1000 x 2 x 500 24 / 32.
+constexpr int64_t kTwoStepSites = 64 * 64 * 64;
+constexpr int64_t kColumnsSites = 400000;
+constexpr int64_t kColumnsSites16 = 2000000;  // D3Q19 in 16-bit storage
+constexpr int64_t kColumnsRows = 64;          // x-rows
+bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz);
+
 // Whether the default for a batch is the two-step kernel: FP32 and FP64 batches
 // large enough in all and box by box, whose planes fill the blocks and whose
 // columns are not all ring.  D3Q19, us per step, one-step against two-step: 256

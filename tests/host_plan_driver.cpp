@@ -87,10 +87,40 @@ static void test_batch_rule()
     EXPECT(!batch_pays(1, 1, 2, wide, 2, 2), "rows at the limit");
 }
 
+static bool single_pays(int lat, int dtype, int64_t nx, int64_t ny, int64_t nz)
+{
+    LatticeInfo L;
+    lattice_info(lat, &L);
+    return columns_pay(L, dtype, nx, ny, nz);
+}
+
+static void test_single_rule()
+{
+    for (int dtype : {0, 1}) {
+        for (int lat : {1, 3}) {
+            for (int64_t a : {64, 80, 100, 127, 128, 160, 201, 255, 256}) EXPECT(single_pays(lat, dtype, a, a, a), "%ld", long(a));
+            EXPECT(!single_pays(lat, dtype, 48, 48, 48) && !single_pays(lat, dtype, 65, 65, 65), "few sites");
+            EXPECT(!single_pays(lat, dtype, 1024, 1024, 1) && !single_pays(lat, dtype, 1000, 1, 1000), "a layer");
+            EXPECT(!single_pays(lat, dtype, 100000, 2, 2), "few rows");
+        }
+        EXPECT(!single_pays(0, dtype, 2000, 2000, 1) && !single_pays(2, dtype, 128, 128, 128), "no column kernel");
+    }
+    for (int dtype : {2, 3}) {
+        // rows of whole lines, whatever ny is
+        for (int64_t ny : {96, 100, 101, 130, 250, 256}) {
+            EXPECT(!single_pays(1, dtype, 256, ny, 256) && !single_pays(1, dtype, 128, ny, 200), "%ld rows", long(ny));
+            EXPECT(!single_pays(1, dtype, 64, 2 * ny, 250), "%ld rows", long(ny));
+        }
+        EXPECT(single_pays(1, dtype, 130, 130, 130) && single_pays(1, dtype, 255, 255, 255), "ragged");
+        EXPECT(!single_pays(3, dtype, 130, 130, 130) && !single_pays(1, dtype, 101, 101, 101), "D3Q15, few sites");
+    }
+}
+
 int main()
 {
     test_column_tiles();
     test_batch_rule();
+    test_single_rule();
     if (g_fail) return 2;
     std::printf("host plan driver: ok\n");
     return 0;

@@ -145,3 +145,14 @@ def test_batched_columns_choice_by_shape():
         for dtype in ("fp32", "fp64"):
             with lbm.Simulation("D3Q19", dims, [0.7] * len(dims), dtype=dtype, torch_memory=False) as sim:
                 assert names[sim.info()["kernel"]] == want, (dims[0], dtype)
+
+
+def test_16_bit_rows_of_whole_lines_keep_the_one_site_step():
+    from paper_2002_02503_amd import lbm
+
+    names = {v: k for k, v in lbm.KERNELS.items()}
+    for dims, want in [((256, 250, 64), "scalar"), ((128, 130, 130), "scalar"), ((64, 250, 250), "scalar"),
+                       ((130, 130, 130), "columns")]:
+        for dtype in ("fp16", "bf16"):
+            with lbm.Simulation("D3Q19", dims, 0.8, dtype=dtype, torch_memory=False) as sim:
+                assert names[sim.info()["kernel"]] == want, (dims, dtype)
