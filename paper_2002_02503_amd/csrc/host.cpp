@@ -153,6 +153,9 @@ bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
     if (!columns_fit(L, dtype, nx, ny, nz) || nx > kMaxSites / ny / nz) return false;
     if (ny < 2 || nz < 2 || ny * nz < kColumnsRows) return false;
     const int64_t sites = nx * ny * nz;
+    int tx = 0, ty = 0;
+    column_tile(size_t(elem), nx, ny, &tx, &ty);
+    if (elem == 8 ? tx * ty < kColumnsLeast64 : tx * ty < kColumnsLeast && (nx > 64 || ty < 16)) return false;
     if (elem == 2) return L.Q == 19 && nx % kTwoStepTileX != 0 && sites >= kColumnsSites16;
     return sites >= (two_step_fits(L, dtype, nx, ny, nz) ? kTwoStepSites : kColumnsSites);
 }

@@ -110,10 +110,18 @@ void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 // does not gain (BF16 130^3 39 / 35).  A box of one layer or of few rows computes
 // the ring for nothing: 1024 x 1024 x 1 37 / 28, 1000 x 1 x 1000 36 / 32, 100000 x 2 x 2
 // 18 / 13, but 512 x 512 x 2 13.9 / 15.6 and 1000 x 2 x 500 24 / 32.
+// A column of few sites leaves the latency of its planes open: below 256 sites
+// only boxes of short rows gain, which leave most lanes of the one-site step idle;
+// in FP64 columns of 16 sites do (two-step / one-site: FP32 4 x 4 x 30000 105 / 61, 8 x
+// 8 x 10000 54 / 44, 64 x 3 x 2188 14.4 / 13.2, 64 x 5 x 1313 12.1 / 13.2, 16 x 8 x 3282
+// 21.6 / 17.8, 16 x 16 x 1641 15.0 / 17.5, 10 x 20 x 2101 22 / 26; BF16 30 x 3 x 22778 122 /
+// 48, 7 x 20 x 14643 104 / 141; FP64 3 x 3 x 60000 207 / 205, 4 x 4 x 30000 109 / 138).
 constexpr int64_t kTwoStepSites = 64 * 64 * 64;
 constexpr int64_t kColumnsSites = 400000;
 constexpr int64_t kColumnsSites16 = 2000000;  // D3Q19 in 16-bit storage
 constexpr int64_t kColumnsRows = 64;          // x-rows
+constexpr int kColumnsLeast = 256;            // sites of a column
+constexpr int kColumnsLeast64 = 16;           // in FP64
 bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz);
 
 // Whether the default for a batch is the two-step kernel: FP32 and FP64 batches

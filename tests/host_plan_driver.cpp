@@ -103,6 +103,13 @@ static void test_single_rule()
             EXPECT(!single_pays(lat, dtype, 1024, 1024, 1) && !single_pays(lat, dtype, 1000, 1, 1000), "a layer");
             EXPECT(!single_pays(lat, dtype, 100000, 2, 2), "few rows");
         }
+        for (int lat : {1, 3}) {
+            EXPECT(!single_pays(lat, dtype, 3, 3, 60000), "narrow");
+            EXPECT(single_pays(lat, dtype, 16, 16, 4000) && single_pays(lat, dtype, 5, 30, 3000), "short rows");
+            EXPECT(single_pays(lat, dtype, 4, 4, 30000) == (dtype == 0), "narrow");
+            EXPECT(single_pays(lat, dtype, 30, 3, 5000) == (dtype == 0), "narrow");
+            EXPECT(single_pays(lat, dtype, 64, 3, 2400) == (dtype == 0), "narrow");
+        }
         EXPECT(!single_pays(0, dtype, 2000, 2000, 1) && !single_pays(2, dtype, 128, 128, 128), "no column kernel");
     }
     for (int dtype : {2, 3}) {
@@ -112,6 +119,8 @@ static void test_single_rule()
             EXPECT(!single_pays(1, dtype, 64, 2 * ny, 250), "%ld rows", long(ny));
         }
         EXPECT(single_pays(1, dtype, 130, 130, 130) && single_pays(1, dtype, 255, 255, 255), "ragged");
+        EXPECT(!single_pays(1, dtype, 12, 12, 20000) && !single_pays(1, dtype, 200, 2, 6000), "narrow");
+        EXPECT(single_pays(1, dtype, 20, 20, 6000) && single_pays(1, dtype, 10, 20, 12000), "short rows");
         EXPECT(!single_pays(3, dtype, 130, 130, 130) && !single_pays(1, dtype, 101, 101, 101), "D3Q15, few sites");
     }
 }
