@@ -156,6 +156,10 @@ bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
     int tx = 0, ty = 0;
     column_tile(size_t(elem), nx, ny, &tx, &ty);
     if (elem == 8 ? tx * ty < kColumnsLeast64 : tx * ty < kColumnsLeast && (nx > 64 || ty < 16)) return false;
+    if (!two_step_fits(L, dtype, nx, ny, nz)) {
+        const bool lines = nx * elem % 128 == 0;
+        if (nz < (elem == 8 ? (sites < kColumnsThin64 ? 2 : 4) : elem == 4 ? (lines ? 4 : 3) : 12)) return false;
+    }
     if (elem == 2) return L.Q == 19 && nx % kTwoStepTileX != 0 && sites >= kColumnsSites16;
     return sites >= (two_step_fits(L, dtype, nx, ny, nz) ? kTwoStepSites : kColumnsSites);
 }

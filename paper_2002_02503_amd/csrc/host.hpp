@@ -110,6 +110,13 @@ void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 // does not gain (BF16 130^3 39 / 35).  A box of one layer or of few rows computes
 // the ring for nothing: 1024 x 1024 x 1 37 / 28, 1000 x 1 x 1000 36 / 32, 100000 x 2 x 2
 // 18 / 13, but 512 x 512 x 2 13.9 / 15.6 and 1000 x 2 x 500 24 / 32.
+// Few planes: a column adds two planes of step 1, and a cut between blocks two
+// more.  Other tiles than the whole 64-column ones gain from three planes on in
+// FP32 (1000 x 1000 x 2 69 / 65, x 3 90 / 98), from four on rows of whole lines (1024 x
+// 300 x 3 26.7 / 25.2, x 4 31.5 / 32.9), in FP64 from four on where the state is past
+// the caches (1000 x 1000 x 3 187 / 168, x 4 222 / 224, 700 x 700 x 3 85 / 95), in 16-bit
+// storage from about twelve (BF16 1000 x 1000 x 4 98 / 81, 700 x 700 x 5 58 / 54, 500 x
+// 500 x 10 49 / 52).
 // A column of few sites leaves the latency of its planes open: below 256 sites
 // only boxes of short rows gain, which leave most lanes of the one-site step idle;
 // in FP64 columns of 16 sites do (two-step / one-site: FP32 4 x 4 x 30000 105 / 61, 8 x
@@ -122,6 +129,7 @@ constexpr int64_t kColumnsSites16 = 2000000;  // D3Q19 in 16-bit storage
 constexpr int64_t kColumnsRows = 64;          // x-rows
 constexpr int kColumnsLeast = 256;            // sites of a column
 constexpr int kColumnsLeast64 = 16;           // in FP64
+constexpr int64_t kColumnsThin64 = 1500000;   // sites of an FP64 state in the caches
 bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz);
 
 // Whether the default for a batch is the two-step kernel: FP32 and FP64 batches

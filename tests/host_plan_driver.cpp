@@ -96,6 +96,8 @@ static bool single_pays(int lat, int dtype, int64_t nx, int64_t ny, int64_t nz)
 
 static void test_single_rule()
 {
+    EXPECT(!single_pays(1, 1, 640, 500, 3) && !single_pays(1, 1, 1024, 300, 2), "few planes on whole lines");
+    EXPECT(single_pays(1, 1, 640, 500, 4) && !single_pays(1, 0, 1000, 1000, 3), "few planes");
     for (int dtype : {0, 1}) {
         for (int lat : {1, 3}) {
             for (int64_t a : {64, 80, 100, 127, 128, 160, 201, 255, 256}) EXPECT(single_pays(lat, dtype, a, a, a), "%ld", long(a));
@@ -110,6 +112,8 @@ static void test_single_rule()
             EXPECT(single_pays(lat, dtype, 30, 3, 5000) == (dtype == 0), "narrow");
             EXPECT(single_pays(lat, dtype, 64, 3, 2400) == (dtype == 0), "narrow");
         }
+        EXPECT(!single_pays(1, dtype, 1000, 1000, 2) && single_pays(1, dtype, 1000, 1000, 4), "few planes");
+        EXPECT(single_pays(1, dtype, 512, 512, 2) && single_pays(1, dtype, 700, 700, 3), "few planes");
         EXPECT(!single_pays(0, dtype, 2000, 2000, 1) && !single_pays(2, dtype, 128, 128, 128), "no column kernel");
     }
     for (int dtype : {2, 3}) {
@@ -121,6 +125,7 @@ static void test_single_rule()
         EXPECT(single_pays(1, dtype, 130, 130, 130) && single_pays(1, dtype, 255, 255, 255), "ragged");
         EXPECT(!single_pays(1, dtype, 12, 12, 20000) && !single_pays(1, dtype, 200, 2, 6000), "narrow");
         EXPECT(single_pays(1, dtype, 20, 20, 6000) && single_pays(1, dtype, 10, 20, 12000), "short rows");
+        EXPECT(!single_pays(1, dtype, 1000, 1000, 4) && !single_pays(1, dtype, 700, 700, 5), "few planes");
         EXPECT(!single_pays(3, dtype, 130, 130, 130) && !single_pays(1, dtype, 101, 101, 101), "D3Q15, few sites");
     }
 }
