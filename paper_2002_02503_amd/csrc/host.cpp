@@ -160,7 +160,12 @@ bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
         const bool lines = nx * elem % 128 == 0;
         if (nz < (elem == 8 ? (sites < kColumnsThin64 ? 2 : 4) : elem == 4 ? (lines ? 4 : 3) : 12)) return false;
     }
-    if (elem == 2) return L.Q == 19 && nx % kTwoStepTileX != 0 && sites >= kColumnsSites16;
+    if (elem == 2) {
+        if (L.Q != 19 || nx % kTwoStepTileX == 0 || sites < kColumnsSites16) return false;
+        const int64_t block = std::min<int64_t>(256, (nx + 63) / 64 * 64);
+        const int64_t lanes = (nx + block - 1) / block * block;  // of the one-site step on a row
+        return !(nx * elem % 32 == 0 && 5 * nx >= 4 * lanes && sites * L.Q * elem >= kColumnsState16);
+    }
     return sites >= (two_step_fits(L, dtype, nx, ny, nz) ? kTwoStepSites : kColumnsSites);
 }
 

@@ -107,7 +107,9 @@ void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 // issue and nothing is gained (FP16 128^3 26.4 / 26, 256^3 209 / 206; also where ny
 // is no multiple of the tile: BF16 128 x 130 x 130 36 / 30); on others D3Q19 needs
 // more sites (BF16 101^3 26 / 24, 130^3 43 / 50, FP16 201 x 150 x 77 41 / 48) and D3Q15
-// does not gain (BF16 130^3 39 / 35).  A box of one layer or of few rows computes
+// does not gain (BF16 130^3 39 / 35); nor do large states with rows of whole 32-byte
+// sectors that fill four fifths of the one-site step's lanes (BF16 160^3 74 / 64,
+// 240^3 285 / 244, but 208 x 120 x 120 50 / 54 and 400 x 200 x 100 163 / 180).  A box of one layer or of few rows computes
 // the ring for nothing: 1024 x 1024 x 1 37 / 28, 1000 x 1 x 1000 36 / 32, 100000 x 2 x 2
 // 18 / 13, but 512 x 512 x 2 13.9 / 15.6 and 1000 x 2 x 500 24 / 32.
 // Few planes: a column adds two planes of step 1, and a cut between blocks two
@@ -126,6 +128,7 @@ void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 constexpr int64_t kTwoStepSites = 64 * 64 * 64;
 constexpr int64_t kColumnsSites = 400000;
 constexpr int64_t kColumnsSites16 = 2000000;  // D3Q19 in 16-bit storage
+constexpr int64_t kColumnsState16 = int64_t(128) << 20;  // bytes: both buffers past the Infinity Cache
 constexpr int64_t kColumnsRows = 64;          // x-rows
 constexpr int kColumnsLeast = 256;            // sites of a column
 constexpr int kColumnsLeast64 = 16;           // in FP64

@@ -126,6 +126,8 @@ static void test_single_rule()
         EXPECT(!single_pays(1, dtype, 12, 12, 20000) && !single_pays(1, dtype, 200, 2, 6000), "narrow");
         EXPECT(single_pays(1, dtype, 20, 20, 6000) && single_pays(1, dtype, 10, 20, 12000), "short rows");
         EXPECT(!single_pays(1, dtype, 1000, 1000, 4) && !single_pays(1, dtype, 700, 700, 5), "few planes");
+        EXPECT(!single_pays(1, dtype, 160, 160, 160) && !single_pays(1, dtype, 240, 240, 240), "rows of whole sectors");
+        EXPECT(single_pays(1, dtype, 208, 120, 120) && single_pays(1, dtype, 400, 200, 100), "in the caches, idle lanes");
         EXPECT(!single_pays(3, dtype, 130, 130, 130) && !single_pays(1, dtype, 101, 101, 101), "D3Q15, few sites");
     }
 }
