@@ -128,7 +128,14 @@ static int widest_piece(int threads) { return std::min(128, threads / 4 - 2); }
 
 void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty)
 {
-    *tx = (nx % kTwoStepTileX == 0) ? kTwoStepTileX : even_piece(nx, widest_piece(two_step_threads(elem)));
+    const int widest = widest_piece(two_step_threads(elem));
+    *tx = (nx % kTwoStepTileX == 0) ? kTwoStepTileX : even_piece(nx, widest);
+    if (elem == 8 && nx % 16 == 0 && *tx % 8 != 0) {
+        // one piece more, if those start on half a line
+        const int64_t more = (nx + *tx - 1) / *tx + 1;
+        const int finer = int((nx + more - 1) / more);
+        if (finer % 8 == 0) *tx = finer;
+    }
     *ty = even_piece(ny, two_step_threads(elem) / (*tx + 2) - 2);
 }
 

@@ -83,7 +83,10 @@ bool columns_fit(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
 // 100^3 21 (100 x 4), 29 (50 x 10), 33 (34 x 17); 255^3 363 (128 x 3), 411 (64 x
 // 8); 160^3 83 (80 x 6 and 160 x 2), 93 (32 x 18); FP64 100^3 38 (100 x 2), 44
 // (50 x 6), 120^3 69 (60 x 5), 84 (120 x 1), 240^3 589 (80 x 3), 912 (120 x 1;
-// one-site step 706), 255^3 542 (85 x 3), 689 (128 x 1).
+// one-site step 706), 255^3 542 (85 x 3), 689 (128 x 1).  FP64 rows of whole lines
+// whose pieces would start elsewhere are cut once more where that mends it: 224^3
+// 490 (56 x 5), 594 (75 x 3; one-site step 573), 400 x 200 x 100 350 (80 x 3), 442
+// (100 x 2).
 void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 
 // Rounds of a compute unit's four SIMDs that a plane of a column tile takes:

@@ -43,6 +43,13 @@ static void test_column_tiles()
                 check_tile(elem, batch_columns_threads(elem), nx, ny, tx, ty);
             }
         }
+        if (elem == 8) {
+            int tx = 0, ty = 0;
+            column_tile(elem, 224, 224, &tx, &ty);
+            EXPECT(tx == 56 && ty == 5, "%d x %d", tx, ty);
+            column_tile(elem, 240, 240, &tx, &ty);
+            EXPECT(tx == 80 && ty == 3, "%d x %d", tx, ty);
+        }
         for (int64_t nx : {int64_t(65537), int64_t(100001), int64_t(1) << 21, (int64_t(1) << 27) + 1}) {
             int tx = 0, ty = 0;
             column_tile(elem, nx, 50, &tx, &ty);
