@@ -137,6 +137,7 @@ struct lbm_ctx {
     int nchunks = 0;
     int chunk_sites = kChunkSites;
     TilePlan tile{};                // plan of the tile kernel (steps = 0: none)
+    bool tile_default = false;      // and it is the default
     int* d_box_chunk_begin = nullptr;
     double* d_partial = nullptr;
     double* d_out = nullptr;
@@ -186,12 +187,12 @@ bool tile_ok(const lbm_ctx* h) { return is_single(h) && h->tile.steps > 0; }
 
 // Without a choice by the caller or the tuner: the one-site step where the
 // caller set a launch shape, which is that step's; else the tile kernel where it
-// has a plan, the two-step kernel where it gains (host.hpp, columns_pay), or the
-// one-site step.
+// has a plan and the two-step kernel where they gain (host.hpp, tile_default and
+// columns_pay), or the one-site step.
 int auto_kernel(const lbm_ctx* h)
 {
     if (h->block > 0 || h->grid > 0) return LBM_KERNEL_SCALAR;
-    if (tile_ok(h)) return LBM_KERNEL_TILE;
+    if (h->tile_default) return LBM_KERNEL_TILE;
     if (!h->columns_pay) return LBM_KERNEL_SCALAR;
     return two_step_ok(h) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_COLUMNS;
 }
@@ -500,9 +501,10 @@ lbm_status create_common(lbm_t* out, int32_t lattice, int32_t nbox, const int64_
                 hipSuccess)
                 return cleanup(fail_hip(e, "copy boxes"));
         }
+        if (nbox == 1 && !tile_plan(L, dtype, dims[0], dims[1], dims[2], h->cus, &h->tile)) h->tile = TilePlan{};
+        h->tile_default = h->tile.steps > 0 && lbm::tile_default(L, dtype, dims[0], dims[1], dims[2], h->tile);
         h->columns_pay = nbox == 1 ? columns_pay(L, dtype, dims[0], dims[1], dims[2])
                                    : batch_columns_pay(L, dtype, nbox, dims);
-        if (nbox == 1 && !tile_plan(L, dtype, dims[0], dims[1], dims[2], h->cus, &h->tile)) h->tile = TilePlan{};
         *out = h;
         return LBM_OK;
     } catch (...) {

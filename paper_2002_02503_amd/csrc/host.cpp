@@ -272,6 +272,15 @@ bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t 
     return false;
 }
 
+bool tile_default(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, const TilePlan& p)
+{
+    if (L.D == 2 || dtype != 0 || p.steps > 2) return true;
+    const int64_t region = tile_region(L, p, nx, p.steps);
+    if (region <= 4 * p.tx * p.ty * p.tz) return true;
+    const int64_t tiles = ((nx + p.tx - 1) / p.tx) * ((ny + p.ty - 1) / p.ty) * ((nz + p.tz - 1) / p.tz);
+    return tiles * region * L.Q * 8 <= kTileRingLoads;
+}
+
 uint64_t geometry_hash(const std::vector<int64_t>& dims)
 {
     uint64_t x = 1469598103934665603ULL;  // FNV-1a over the dims

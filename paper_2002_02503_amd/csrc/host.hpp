@@ -200,6 +200,16 @@ constexpr int64_t kTileRounds3d = 4;
 constexpr int64_t kTileShare16 = 1024;
 bool tile_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, int cus, TilePlan* out);
 
+// Whether a box with a plan takes it by default.  In FP64, where a site's values
+// are twice as long, a two-step launch whose first step reads more than four
+// times the tile loses once those loads pass 8 MB: us per step, one-site against the
+// plan, D3Q19 64 x 10 x 24 (64 x 1 x 1 tiles, 21 MB) 3.82 / 4.37, 41 x 115 x 4 (41 x 2 x 1,
+// 17 MB) 4.30 / 4.67, 64 x 4 x 23 (8.1 MB) 3.28 / 3.34, 64 x 7 x 8 (4.9 MB) 3.18 / 3.15, 42 x
+// 10 x 10 (5.7 MB) 3.42 / 3.03; with at most four times, 32^3 (20 MB) 4.48 / 3.86;
+// three-step launches gain (17 x 17 x 20 3.46 / 2.36).
+constexpr int64_t kTileRingLoads = int64_t(8) << 20;
+bool tile_default(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, const TilePlan& p);
+
 // The argument checks of lbm_create / lbm_create_batch for nbox boxes
 // (dims: nbox * 3, tau: nbox).  True when every box is valid; otherwise false
 // with the reason in *why.

@@ -139,11 +139,32 @@ static void test_single_rule()
     }
 }
 
+// Whether the box has a tile plan and takes it by default.
+static bool tile_taken(int lat, int dtype, int64_t nx, int64_t ny, int64_t nz)
+{
+    LatticeInfo L;
+    lattice_info(lat, &L);
+    TilePlan p;
+    const bool has = tile_plan(L, dtype, nx, ny, nz, 256, &p);
+    EXPECT(has, "%ld x %ld x %ld", long(nx), long(ny), long(nz));
+    return has && tile_default(L, dtype, nx, ny, nz, p);
+}
+
+static void test_tile_rule()
+{
+    EXPECT(tile_taken(0, 0, 64, 64, 1) && tile_taken(0, 0, 1024, 1024, 1), "D2Q9");
+    EXPECT(tile_taken(1, 0, 16, 16, 16) && tile_taken(1, 0, 32, 32, 32) && tile_taken(1, 0, 17, 17, 20), "FP64");
+    for (int lat : {1, 3}) EXPECT(!tile_taken(lat, 0, 64, 10, 24) && !tile_taken(lat, 0, 64, 3, 72), "mostly ring");
+    EXPECT(!tile_taken(1, 0, 41, 115, 4), "mostly ring");
+    for (int dtype : {1, 2, 3}) EXPECT(tile_taken(1, dtype, 64, 10, 24) && tile_taken(1, dtype, 41, 115, 4), "half the bytes");
+}
+
 int main()
 {
     test_column_tiles();
     test_batch_rule();
     test_single_rule();
+    test_tile_rule();
     if (g_fail) return 2;
     std::printf("host plan driver: ok\n");
     return 0;
