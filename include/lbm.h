@@ -254,10 +254,11 @@ lbm_status lbm_set_kernel(lbm_t h, int32_t kernel);
  * applies, the two-row (ny even) and row-wave steps.  Batch: 64/128/256 threads
  * per block with one wave per 64-site block of the layout, and
  * LBM_KERNEL_COLUMNS where it applies.  The state is saved before and restored after, so t and the
- * populations are unchanged (all candidates compute the same bits).  Choices are appended to the text file `cache_path` (NULL: the
- * path in the environment variable LBM_TUNE_CACHE, or no cache); a later call
- * with the same lattice, dtype, K, collision kind and geometry reuses the
- * cached choice without timing.  Needs an initialised handle (LBM_ESTATE
+ * populations are unchanged (all candidates compute the same bits).  Choices are
+ * appended to the text file `cache_path` (NULL: the path in the environment
+ * variable LBM_TUNE_CACHE, or no cache); a later call with the same lattice,
+ * dtype, K, collision kind and geometry reuses the cached choice without timing,
+ * unless another version of the library, with other candidates, made it.  Needs an initialised handle (LBM_ESTATE
  * otherwise); allocates one state-sized scratch buffer while timing. */
 lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path);
 

@@ -1143,13 +1143,17 @@ lbm_status lbm_step(lbm_t h, int64_t n)
 
 namespace {
 
+// Number of the candidate set that lbm_tune times, part of a cache entry's key:
+// an entry made when a kernel or one of its plans did not exist yet would keep
+// the choice of then for good.  Raise it when either changes.
+constexpr int kTuneCandidates = 2;
 
 std::string tune_key(const lbm_ctx* h)
 {
     char buf[256];
-    snprintf(buf, sizeof(buf), "lattice=%d dtype=%d K=%d kind=%d nbox=%d nsites=%lld geometry=%016llx",
+    snprintf(buf, sizeof(buf), "lattice=%d dtype=%d K=%d kind=%d nbox=%d nsites=%lld geometry=%016llx candidates=%d",
              h->lattice, h->dtype, h->K, step_kind(h), h->nbox, (long long)h->nsites,
-             (unsigned long long)geometry_hash(h));
+             (unsigned long long)geometry_hash(h), kTuneCandidates);
     return buf;
 }
 

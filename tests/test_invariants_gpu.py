@@ -258,3 +258,20 @@ def test_tuning_cache_with_bad_entries(tmp_path):
         sim.step(12)
         r, uu = sim.moments()
     assert np.array_equal(r, ref[0]) and np.array_equal(uu, ref[1])
+
+
+def test_tuning_cache_of_another_candidate_set(tmp_path):
+    """An entry without the mark of this library's candidates (an older file) is
+    not taken: the call times them and appends its own choice."""
+    rho, u = _fields((24, 20, 9), 14)
+    cache = tmp_path / "tune.txt"
+    with lbm.Simulation("D3Q19", (24, 20, 9), 0.6, dtype="fp32") as sim:
+        sim.init(rho, u).tune(steps=2, cache=str(cache))
+    key = open(cache).read().splitlines()[-1].split(" | ")[0]
+    old = key[:key.index(" geometry=") + len(" geometry=") + 16]
+    cache.write_text(old + f" | {lbm.KERNELS['scalar']} 64 0\n")
+    with lbm.Simulation("D3Q19", (24, 20, 9), 0.6, dtype="fp32") as sim:
+        sim.init(rho, u).tune(steps=2, cache=str(cache))
+        sim.tune(steps=2, cache=str(cache))
+    lines = open(cache).read().splitlines()
+    assert len(lines) == 2 and lines[1].startswith(key + " | ")
