@@ -249,9 +249,10 @@ lbm_status lbm_set_kernel(lbm_t h, int32_t kernel);
  * events, in three interleaved rounds, and keep the candidate with the fastest
  * round.  Single box: the scalar step at 64/128/256 threads per block, the
  * in-place and twist steps at 256, all three at one whole x-row per block when
- * nx rounds up to 192 lanes, and either the tile kernel, or the two-step kernel
- * (on columns of any size where nx and ny do not fit it), or, where neither
- * applies, the two-row (ny even) and row-wave steps.  Batch: 64/128/256 threads
+ * nx rounds up to 192 lanes, the tile kernel where it has a plan, else the
+ * two-step kernel (on columns of any size where nx and ny do not fit it) where
+ * that applies, and, where neither is the default, the two-row (ny even) and
+ * row-wave steps.  Batch: 64/128/256 threads
  * per block with one wave per 64-site block of the layout, and
  * LBM_KERNEL_COLUMNS where it applies.  The state is saved before and restored after, so t and the
  * populations are unchanged (all candidates compute the same bits).  Choices are

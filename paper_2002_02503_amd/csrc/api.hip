@@ -1217,9 +1217,12 @@ lbm_status lbm_tune(lbm_t h, int32_t steps, const char* cache_path)
                 cand.push_back({LBM_KERNEL_TILE, 0, 0});
             } else if (columns_ok(h)) {
                 cand.push_back({two_step_ok(h) ? LBM_KERNEL_TWO_STEP : LBM_KERNEL_COLUMNS, 0, 0});
-            } else {
-                // one-step forms that were never the fastest where one of the
-                // above runs
+            }
+            if (!h->tile_default && !h->columns_pay) {
+                // one-step forms that are the fastest on some boxes where neither
+                // of the above gains (D3Q19, us per step, against the best of the
+                // others: BF16 32 x 556 x 23 row-wave 9.4 / 11.1, FP16 64^3 two-row
+                // 5.9 / 6.4, FP32 9 x 402 x 10 6.0 / 6.4)
                 if (h->dims[1] % 2 == 0) cand.push_back({LBM_KERNEL_TWO_ROW, 256, 0});
                 if (row_wave_sites(h)) cand.push_back({LBM_KERNEL_ROW_WAVE, 0, 0});
             }
