@@ -275,3 +275,32 @@ def test_tuning_cache_of_another_candidate_set(tmp_path):
         sim.tune(steps=2, cache=str(cache))
     lines = open(cache).read().splitlines()
     assert len(lines) == 2 and lines[1].startswith(key + " | ")
+
+
+@pytest.mark.parametrize("K", [2, 3])
+def test_fp32_rounding_errors_of_the_momentum_do_not_add_up(K):
+    """The mean of the momentum (and density) after 100 steps in FP32 against
+    the same run in FP64.  A site's populations, of size G ~ W u / T0 <= 2 in
+    stored units, are rounded to half a unit in the last place of 1 .. 2, on
+    average 2^-23 / sqrt(12), so an unbiased error of the momentum is about
+    sqrt(6) 2^-23 / sqrt(12) / 36 a site and step (six populations carry each
+    component, stored in units of 1/36) and 1/sqrt(sites) of it in the mean; the
+    bound is four times its sum over the steps.  A bias would grow with the
+    steps instead of their root."""
+    nx, ny, steps = 96, 64, 100
+    unbiased = np.sqrt(6 / 12) * 2.0**-23 / 36 * np.sqrt(steps / (nx * ny))
+    y, x = np.meshgrid(np.arange(ny) * 2 * np.pi / ny, np.arange(nx) * 2 * np.pi / nx, indexing="ij")
+    rho = (1 + 0.005 * np.cos(x + 2 * y))[None]
+    drift = []
+    for tau in (0.51, 0.6, 0.8, 1.0):
+        for seed, flow in ((1, 0.0), (2, 0.1), (3, 0.02), (4, 0.05), (5, 0.07), (6, 0.0)):
+            rng = np.random.default_rng(seed)
+            d = rng.normal(size=2)
+            u = np.stack([0.03 * np.sin(y * rng.integers(0, 3) + x * rng.integers(1, 4) + rng.uniform(0, 6))
+                          for _ in range(2)]) + flow * (d / np.linalg.norm(d))[:, None, None]
+            mean = {}
+            for dtype in ("fp64", "fp32"):
+                with lbm.Simulation("D2Q9", (nx, ny, 1), tau, dtype=dtype, K=K) as sim:
+                    mean[dtype] = sim.init(rho, u[:, None]).step(steps).totals()[0, :3] / (nx * ny)
+            drift.append(np.abs(mean["fp32"] - mean["fp64"]).max())
+    assert np.mean(drift) <= 4 * unbiased, (np.mean(drift), unbiased)
