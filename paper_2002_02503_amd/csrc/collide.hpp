@@ -56,17 +56,19 @@ __device__ __forceinline__ R fused(R a, R b, R c)
 
 // x / N in double, rounded as the division is, for a small integer N: with the
 // correctly rounded 1 / N the quotient is off by at most one unit in the last
-// place and its exact remainder corrects it (Markstein).  An infinite x leaves
-// no remainder and keeps the quotient.  An FP64 division is some 25
-// instructions.
+// place and its exact remainder corrects it (Markstein).  A quotient below the
+// normal numbers can lie half-way between two of its coarser neighbours, where
+// the rounded 1 / N may choose the other one: it is within one unit.  An infinite x leaves
+// no remainder and keeps the quotient; the remainder is taken with the sign that
+// lets a zero keep its own.  An FP64 division is some 25 instructions.
 template <int N>
-__device__ __forceinline__ double over(double x)
+__host__ __device__ __forceinline__ double over(double x)
 {
     constexpr double inv = 1.0 / N;
     const double q = x * inv;
     if constexpr ((N & (N - 1)) == 0) return q;
-    const double r = __builtin_fma(-double(N), q, x);
-    return r == r ? __builtin_fma(r, inv, q) : q;
+    const double r = __builtin_fma(double(N), q, -x);
+    return r == r ? __builtin_fma(-r, inv, q) : q;
 }
 
 // Sparse dot products with compile-time integer coefficients: zero terms are

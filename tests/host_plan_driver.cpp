@@ -1,11 +1,16 @@
 // Check the plans that the multi-step kernels are launched with
 // (paper_2002_02503_amd/csrc/host.cpp), which the kernels rely on unchecked, for
 // tests/test_host_plans.py: column tiles over all row lengths, and the shapes for
-// which a default is taken.  A failed expectation exits 2.
+// which a default is taken; and the division by a constant that set-up and
+// readers use.  A failed expectation exits 2.
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
+#include <limits>
+#include <random>
 #include <vector>
 
+#include "collide.hpp"
 #include "host.hpp"
 
 using namespace lbm;
@@ -159,12 +164,50 @@ static void test_tile_rule()
     for (int dtype : {1, 2, 3}) EXPECT(tile_taken(1, dtype, 64, 10, 24) && tile_taken(1, dtype, 41, 115, 4), "half the bytes");
 }
 
+// over<N> gives the bits of the division, signed zeros included; a subnormal
+// quotient is the correction rounded to the subnormal numbers' spacing, so where
+// x / N lies half-way between two of them it may be the other one.
+template <int N>
+static void test_over()
+{
+    auto same = [](double x) {
+        const double a = over<N>(x), b = x / double(N);
+        const double least = std::numeric_limits<double>::min();
+        const bool subnormal = b != 0.0 && b > -least && b < least;
+        EXPECT(std::memcmp(&a, &b, sizeof(a)) == 0 || (a != a && b != b) ||
+                   (subnormal && a - b <= std::numeric_limits<double>::denorm_min() &&
+                    b - a <= std::numeric_limits<double>::denorm_min()),
+               "%a / %d: %a, not %a", x, N, a, b);
+    };
+    const double inf = std::numeric_limits<double>::infinity(), big = std::numeric_limits<double>::max();
+    const double tiny = std::numeric_limits<double>::denorm_min(), least = std::numeric_limits<double>::min();
+    for (double x : {0.0, inf, big, tiny, 3 * tiny, double(N) * tiny, least, least * N, 1.0, double(N), std::numeric_limits<double>::quiet_NaN()}) {
+        same(x);
+        same(-x);
+    }
+    std::mt19937_64 rng(N);
+    for (int k = 0; k < 200000; ++k) {
+        uint64_t bits = rng();
+        double x;
+        std::memcpy(&x, &bits, sizeof(x));
+        same(x);                              // any exponent
+        same(double(int64_t(bits >> 8)) / 1e18);  // ordinary values
+    }
+}
+
 int main()
 {
     test_column_tiles();
     test_batch_rule();
     test_single_rule();
     test_tile_rule();
+    test_over<2>();
+    test_over<6>();
+    test_over<24>();
+    test_over<120>();
+    test_over<36>();
+    test_over<72>();
+    test_over<6480>();
     if (g_fail) return 2;
     std::printf("host plan driver: ok\n");
     return 0;
