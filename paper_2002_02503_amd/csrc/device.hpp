@@ -113,8 +113,10 @@ __device__ __forceinline__ T* at32(T* p, unsigned i)
     return reinterpret_cast<T*>(reinterpret_cast<B*>(p) + unsigned(i * unsigned(sizeof(T))));
 }
 
-// Periodic wrap of a coordinate v in [-3, n + 2] onto [0, n).  One period off
-// at most from n = 3 on; for n = 1 and 2 the mask n - 1 does it (a remainder
+// Periodic wrap of a coordinate v onto [0, n): v in [-n, 2 n) from n = 3 on (the
+// one-site kernels pass at most three sites past the box, rings of several steps
+// and narrower last columns more), any v for n = 1 and 2, where the mask n - 1
+// does it (a remainder
 // in their place put some 25 instructions for each wrapped coordinate into
 // every kernel).
 __device__ __forceinline__ int wrap_coord(int v, int n)

@@ -1,9 +1,12 @@
 // Check the plans that the multi-step kernels are launched with
 // (paper_2002_02503_amd/csrc/host.cpp), which the kernels rely on unchecked, for
-// tests/test_host_plans.py: column tiles over all row lengths, and the shapes for
-// which a default is taken; and the division by a constant that set-up and
+// tests/test_host_plans.py: column tiles over all row lengths, tile plans over box
+// sizes, lattices, types and compute units, with the limits that bound the
+// kernels' threads, LDS, offsets and wrapped coordinates; the shapes for which a
+// default is taken; and the division by a constant that set-up and
 // readers use.  A failed expectation exits 2.
 #include <cstdint>
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <limits>
@@ -33,6 +36,81 @@ static void check_tile(size_t elem, int threads, int64_t nx, int64_t ny, int tx,
     EXPECT(tx >= 1 && ty >= 1 && tx <= nx && ty <= ny, "%zu bytes, %ld x %ld: %d x %d", elem, long(nx), long(ny), tx, ty);
     EXPECT((tx + 2) * (ty + 2) <= threads, "%zu bytes, %ld x %ld: %d x %d", elem, long(nx), long(ny), tx, ty);
     EXPECT(ty >= 2 || ny == 1, "%zu bytes, %ld x %ld: %d x %d", elem, long(nx), long(ny), tx, ty);
+    // the ring of a last column, and its neighbours, are within a period of the box
+    const int64_t x_end = (nx + tx - 1) / tx * tx, y_end = (ny + ty - 1) / ty * ty;
+    EXPECT((nx < 3 || x_end < 2 * nx) && (ny < 3 || y_end < 2 * ny), "%ld x %ld: %d x %d", long(nx), long(ny), tx, ty);
+}
+
+// A tile plan, whichever box it is for.
+static void check_plan(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_t nz, const TilePlan& p)
+{
+    const int64_t elem = int64_t(storage_bytes(dtype)), n[3] = {nx, ny, nz}, t[3] = {p.tx, p.ty, p.tz};
+    bool ok = p.steps >= 2 && p.steps <= kTileMaxSteps && p.block >= 64 && p.block <= 1024 && p.block % 64 == 0;
+    // the regions of a full tile: the stored one in LDS, the later ones with one thread per site
+    int64_t region = 1, second = 1;
+    for (int a = 0; a < L.D; ++a) {
+        const bool wraps = a == 0 && p.tx == nx;  // inside the tile
+        const int64_t ring = wraps ? 0 : p.steps - 1;
+        ok = ok && t[a] >= 1 && t[a] <= n[a];
+        region *= t[a] + 2 * ring;
+        second *= t[a] + 2 * std::max<int64_t>(ring - 1, 0);
+        // ring sites within a period of the box, for three sites and more
+        ok = ok && (n[a] < 3 || (ring <= n[a] && n[a] - 1 + ring < 2 * n[a]));
+    }
+    ok = ok && region * L.Q * elem <= 160 * 1024 && region < (1 << 15) && second <= p.block;
+    ok = ok && tile_region(L, p, nx, p.steps) == region && (L.D == 3 || nz == 1);
+    // offsets in 32 bits
+    ok = ok && double(nx) * double(ny) * double(nz) * L.Q * double(elem) <= 4294967296.0;
+    // a launch of fewer steps is a smaller region
+    for (int k = 2; k < p.steps; ++k) ok = ok && tile_region(L, p, nx, k) < region;
+    EXPECT(ok, "D%dQ%d dtype %d %ld x %ld x %ld: %d x %d x %d, %d steps, %d threads", L.D, L.Q, dtype, long(nx), long(ny),
+           long(nz), p.tx, p.ty, p.tz, p.steps, p.block);
+}
+
+static void test_tile_plans()
+{
+    const int64_t sides[] = {1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 129, 200, 511, 1000, 4097, 65535};
+    const int64_t wide[] = {100001, 1 << 21, (int64_t(1) << 27) + 1, (int64_t(1) << 29), INT32_MAX};
+    int plans = 0;
+    for (int lat = 0; lat < 4; ++lat) {
+        LatticeInfo L;
+        lattice_info(lat, &L);
+        for (int dtype = 0; dtype < 4; ++dtype) {
+            for (int cus : {1, 64, 256, 304}) {
+                auto one = [&](int64_t nx, int64_t ny, int64_t nz) {
+                    TilePlan p{};
+                    if (!tile_plan(L, dtype, nx, ny, nz, cus, &p)) return;
+                    EXPECT(L.R == 1, "a ring of one site");
+                    check_plan(L, dtype, nx, ny, nz, p);
+                    ++plans;
+                };
+                for (int64_t nx : sides)
+                    for (int64_t ny : sides)
+                        for (int64_t nz : sides)
+                            if (L.D == 3 || nz == 1) one(nx, ny, nz);
+                for (int64_t nx : wide)
+                    for (int64_t ny : {int64_t(1), int64_t(2), int64_t(65535)}) one(nx, ny, 1);
+            }
+        }
+    }
+    EXPECT(plans > 10000, "%d plans", plans);
+    // D2Q9 on both sides of 4 GiB (36 bytes a site in FP32)
+    LatticeInfo L;
+    lattice_info(0, &L);
+    TilePlan p{};
+    EXPECT(tile_plan(L, 1, 10922, 10922, 1, 256, &p) && !tile_plan(L, 1, 10923, 10923, 1, 256, &p), "4 GiB");
+}
+
+static void test_column_limits()
+{
+    // the two-step kernel's offsets inside a z-plane, 19 * 4 bytes a site
+    LatticeInfo L;
+    lattice_info(1, &L);
+    const int64_t most = ((int64_t(1) << 31) - 1) / (19 * 4);
+    EXPECT(columns_fit(L, 1, most, 1, 9) && !columns_fit(L, 1, most + 1, 1, 9), "one row");
+    EXPECT(columns_fit(L, 1, 5315, 5316, 2) && !columns_fit(L, 1, 5316, 5316, 2), "a plane");
+    EXPECT(!columns_fit(L, 1, 0, 8, 8) && !columns_fit(L, 1, 8, -1, 8) && !columns_fit(L, 4, 8, 8, 8), "no box, no type");
+    EXPECT(!columns_fit(L, 1, INT64_MAX, INT64_MAX, INT64_MAX), "beyond 2^31");
 }
 
 static void test_column_tiles()
@@ -198,6 +276,8 @@ static void test_over()
 int main()
 {
     test_column_tiles();
+    test_column_limits();
+    test_tile_plans();
     test_batch_rule();
     test_single_rule();
     test_tile_rule();
