@@ -95,8 +95,9 @@ KERNEL_SYMBOLS = {"scalar": "k_step", "row_wave": "k_step_vec", "in_place": "k_s
                   "columns": "k_step2"}
 BATCH_SYMBOLS = {"scalar": "k_step_batch", "columns": "k_step2_batch"}
 # time steps one launch of a kernel takes (the two-step kernel: two; per-launch
-# figures count both)
-STEPS_PER_LAUNCH = {"two_step": 2, "columns": 2}
+# figures count both); the tile kernel, whose steps follow the box, runs none of
+# the workloads here
+STEPS_PER_LAUNCH = {"scalar": 1, "row_wave": 1, "in_place": 1, "two_row": 1, "twist": 1, "two_step": 2, "columns": 2}
 STORAGE_CTYPE = {"fp64": "double", "fp32": "float", "fp16": "_Float16", "bf16": "bf16_t"}
 
 
@@ -141,7 +142,7 @@ def measure_box(lattice, dims, tau, dtype, rho, u, steps, warmup, tune=True, **k
     return {"value": mlups, "unit": "MLUPS", "ms_per_step": ms, "steps": steps,
             "bytes_per_site_update": bytes_site, "nsites": nsites, "achieved_GBs": gbs,
             "roofline_frac": gbs / PEAK_HBM_GBS, "kernel": kernel,
-            "steps_per_launch": STEPS_PER_LAUNCH.get(kernel, 1),
+            "steps_per_launch": STEPS_PER_LAUNCH[kernel],
             "block": info["block"], "grid": info["grid"], "conservation": conservation,
             "launches": {"graph_chunk": int(info["graph_chunk"]), "graph_launches": steps // int(info["graph_chunk"]),
                          "direct_launches": steps % int(info["graph_chunk"]), "warmup_direct_launches": warmup},

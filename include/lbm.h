@@ -67,11 +67,12 @@ typedef enum {
     LBM_COLLISION_BGK = 1        /* eq. BGK, f' = f - (f - f^eq)/tau, with the same truncated f^eq */
 } lbm_collision;
 
-/* Step-kernel variants for a single box (lbm_set_kernel). */
+/* Step-kernel variants (lbm_set_kernel): of a single box; batches take AUTO,
+ * SCALAR and COLUMNS. */
 typedef enum {
-    LBM_KERNEL_AUTO = 0,      /* until a tuned choice is set: the tile kernel where it applies, the two-step
-                                 kernel (on columns of any size where nx and ny do not fit it) where the box
-                                 is large enough to gain, else the scalar step, also where a launch shape
+    LBM_KERNEL_AUTO = 0,      /* until a tuned choice is set: the tile kernel or the two-step kernel (on
+                                 columns of any size where nx and ny do not fit it) where the box's sizes and
+                                 storage type let it gain, else the scalar step, also where a launch shape
                                  was set */
     LBM_KERNEL_SCALAR = 1,    /* one site per thread, 4/8-byte accesses */
     LBM_KERNEL_ROW_WAVE = 2,  /* V sites per lane, 8/16-byte accesses, x-neighbours by lane shuffle */
@@ -104,8 +105,9 @@ typedef struct {
     int64_t t;                   /* steps taken since lbm_init */
     int64_t bytes_per_site_update; /* 2 * Q * sizeof(storage): one read + one write per population */
     uint64_t state_bytes;        /* bytes of one population buffer (see lbm_state_bytes) */
-    int32_t block, grid;         /* launch shape in use (threads per block; batched grid size, 0 = one wave per
-                                    tile; for LBM_KERNEL_TWO_STEP its number of blocks) */
+    int32_t block, grid;         /* launch shape in use (threads per block of the one-step kernels; batched grid
+                                    size, 0 = one wave per tile; for LBM_KERNEL_TWO_STEP and LBM_KERNEL_COLUMNS of a
+                                    single box their number of blocks) */
     int32_t graph_chunk;         /* steps per captured graph */
     int32_t kernel;              /* step kernel in use (lbm_kernel, never AUTO) */
     int32_t collision;           /* lbm_collision in use */
@@ -125,8 +127,8 @@ typedef struct {
  * LBM_ENODEV, LBM_EDEVICE, LBM_ENOMEM. */
 lbm_status lbm_create(lbm_t* out, int32_t lattice, const int64_t dims[3], double tau, int32_t dtype);
 
-/* Create nbox independent periodic boxes advanced together by one launch per
- * step.  dims: nbox * 3 int64 (nx, ny, nz per box); tau: nbox doubles.  Same
+/* Create nbox independent periodic boxes advanced together, by one launch per
+ * step or, with LBM_KERNEL_COLUMNS, per two steps.  dims: nbox * 3 int64 (nx, ny, nz per box); tau: nbox doubles.  Same
  * rules per box as lbm_create.  Boxes are stored back to back, in order. */
 lbm_status lbm_create_batch(lbm_t* out, int32_t lattice, int32_t nbox, const int64_t* dims,
                             const double* tau, int32_t dtype);
@@ -203,8 +205,8 @@ lbm_status lbm_set_graph_chunk(lbm_t h, int32_t steps);
  * for batches, the number of blocks of the persistent step kernel (0 = enough
  * blocks for every tile to get its own wave; a batch tile is one wave's work:
  * one 64-site block of a box's layout).  For a single box the grid is the
- * number of blocks of LBM_KERNEL_TWO_STEP (0 = one per compute unit; its
- * blocks have a fixed size).  Only before lbm_init. */
+ * number of blocks of LBM_KERNEL_TWO_STEP and LBM_KERNEL_COLUMNS (0 = one per
+ * compute unit; their blocks have a fixed size).  Only before lbm_init. */
 lbm_status lbm_set_launch(lbm_t h, int32_t block, int32_t grid);
 
 /* Choose the single-box step kernel.  All variants compute the same bits.
@@ -219,7 +221,8 @@ lbm_status lbm_set_launch(lbm_t h, int32_t block, int32_t grid);
  * natural layout (rearranged on the host).  Switching kernels later (lbm_tune)
  * allocates the second buffer.  Batches always use the batched kernel (one
  * wave per 64-site block) or, two steps per launch, LBM_KERNEL_COLUMNS, which
- * LBM_KERNEL_AUTO takes for large FP32 and FP64 batches; for them the other
+ * LBM_KERNEL_AUTO takes for large FP32 and FP64 batches whose boxes are not thin
+ * or narrow; for them the other
  * variants but LBM_KERNEL_SCALAR are LBM_EINVAL.
  * LBM_KERNEL_TWIST (single box) also steps inside one buffer.  The state is
  * kept in twisted layouts: population i of site x sits at site x + b_i, b_i
@@ -234,9 +237,14 @@ lbm_status lbm_set_launch(lbm_t h, int32_t block, int32_t grid);
  * one step of the scalar kernel; the state stays in the natural layout.
  * LBM_KERNEL_COLUMNS needs D3Q15 or D3Q19 and, for every box, one z-plane of
  * populations below 2 GiB, else LBM_EINVAL.  It also steps batches.
- * LBM_KERNEL_TILE needs a single D2Q9, D3Q15 or D3Q19 box whose state is below
- * 4 GiB (D2Q9 of any other size; in 3-D at most 160 sites per compute unit),
- * else LBM_EINVAL.  The library chooses the tile and the steps per launch; the
+ * LBM_KERNEL_TILE needs a single D2Q9, D3Q15 or D3Q19 box for which the library
+ * has a plan, else LBM_EINVAL.  It has one for states of at most 4 GiB: D2Q9 in
+ * FP64 and FP32 of any size, but a single row (ny = 1) only where its tiles are
+ * no more than the compute units, and in 16-bit storage at most 1024 sites per
+ * compute unit; in 3-D at most 160 sites per compute unit, rows of at most 64
+ * sites, and a tile's regions within four rounds of 256 threads per compute unit
+ * (on 256 compute units 32^3 has a plan, 33^3 and 200 x 200 x 1 have none).  The
+ * library chooses the tile and the steps per launch; the
  * state stays in the natural layout, and a captured graph holds whole launches
  * (the largest multiple of a launch's steps within the graph chunk).
  * May be called at any time: on an initialised handle the state is first
