@@ -135,7 +135,7 @@ struct lbm_ctx {
     // reductions
     ChunkDesc* d_chunks = nullptr;
     int nchunks = 0;
-    int chunk_sites = kChunkSites;
+    int chunk_sites = 0;            // of the largest chunk
     TilePlan tile{};                // plan of the tile kernel (steps = 0: none)
     bool tile_default = false;      // and it is the default
     int* d_box_chunk_begin = nullptr;
@@ -450,7 +450,6 @@ lbm_status create_common(lbm_t* out, int32_t lattice, int32_t nbox, const int64_
                 n += (dims[3 * b] * dims[3 * b + 1] * dims[3 * b + 2] + chunk - 1) / chunk;
             if (n <= kManyChunks) break;
         }
-        h->chunk_sites = chunk;
         std::vector<ChunkDesc> chunks;
         std::vector<int> begin;
         for (int b = 0; b < nbox; ++b) {
@@ -469,6 +468,7 @@ lbm_status create_common(lbm_t* out, int32_t lattice, int32_t nbox, const int64_
                     c.z0 = int(c.row0 / dims[1]);
                 }
                 chunks.push_back(c);
+                h->chunk_sites = std::max(h->chunk_sites, c.count);
             }
         }
         begin.push_back(int(chunks.size()));
