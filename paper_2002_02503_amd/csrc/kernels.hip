@@ -12,6 +12,8 @@
 // 2 Q S bytes per site, far below the FP32 ridge of the chip), so it uses no
 // matrix cores: every population is read once (pull form of eq. lbe, periodic
 // wrap) and written once, and the collision runs entirely in registers.
+#include <algorithm>
+
 #include "device.hpp"
 #include "step_launch.hpp"
 
@@ -20,8 +22,32 @@ namespace lbm {
 // ---------------------------------------------------------------------------
 // Set-up, moments and reductions work on chunks: runs of consecutive sites
 // of one box.  The reductions take one block per chunk; set-up and moments one
-// thread per site, grid (chunks, blocks per chunk).
+// thread per site, `slices` blocks per chunk.
 // ---------------------------------------------------------------------------
+
+// Blocks run through the slices of a chunk before the next chunk, so those at
+// work at a time are neighbours in memory: cut into chunks first, D3Q19 moments
+// took, us a call within a run of steps, 333 against 281 (256^3 FP32), 221 against
+// 185 (FP16) and, in a batch of 500 boxes of 40^3, whose boxes share the lines of
+// their fields, 430 against 353 (FP16).  A row of the grid holds kGridChunks
+// chunks, so that no dimension comes near 2^32 threads.
+constexpr int kGridChunks = 32768;
+
+static dim3 chunk_grid(int nchunks, unsigned slices)
+{
+    return dim3(slices * unsigned(std::min(nchunks, kGridChunks)),
+                unsigned((nchunks + kGridChunks - 1) / kGridChunks));
+}
+
+__device__ __forceinline__ int block_chunk(unsigned slices)
+{
+    return int(blockIdx.y) * kGridChunks + int(blockIdx.x / slices);
+}
+
+__device__ __forceinline__ int block_site(unsigned slices)
+{
+    return int(blockIdx.x % slices) * int(blockDim.x) + int(threadIdx.x);
+}
 
 // Place of site k of a chunk: its block (for a single box its x-row) and its
 // position there, and for a single box y and z.  The chunk carries its first
@@ -96,14 +122,17 @@ __device__ __forceinline__ long long layout_elem(const Around<L>& at, const BoxD
 template <class L, class S, int K, int LAYOUT>
 __global__ __launch_bounds__(256) void k_init(const double* __restrict__ rho, const double* __restrict__ u,
                                               S* __restrict__ dst, const ChunkDesc* __restrict__ chunks,
-                                              const BoxDesc* __restrict__ boxes, long long nsites)
+                                              const BoxDesc* __restrict__ boxes, long long nsites, int nchunks,
+                                              unsigned slices)
 {
     using ST = Store<S>;
     static_assert(LAYOUT == kNatural || LAYOUT == kTwistEven, "init writes a layout of time 0");
-    const ChunkDesc ch = chunks[blockIdx.x];
+    const int c = block_chunk(slices);
+    if (c >= nchunks) return;
+    const ChunkDesc ch = chunks[c];
     const BoxDesc b = boxes[ch.box];
     S* base = dst + b.mem;
-    const int k = int(blockIdx.y) * int(blockDim.x) + int(threadIdx.x);
+    const int k = block_site(slices);
     if (k >= ch.count) return;
     const long long s = ch.start + k;
     const SitePos pos = locate<LAYOUT != kNatural>(ch, k, b);
@@ -197,12 +226,15 @@ __device__ __forceinline__ void stored_site_moments(const S* __restrict__ base, 
 template <class L, class S, int LAYOUT>
 __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ src, double* __restrict__ rho,
                                                  double* __restrict__ u, const ChunkDesc* __restrict__ chunks,
-                                                 const BoxDesc* __restrict__ boxes, long long nsites)
+                                                 const BoxDesc* __restrict__ boxes, long long nsites, int nchunks,
+                                                 unsigned slices)
 {
-    const ChunkDesc ch = chunks[blockIdx.x];
+    const int c = block_chunk(slices);
+    if (c >= nchunks) return;
+    const ChunkDesc ch = chunks[c];
     const BoxDesc b = boxes[ch.box];
     const S* base = src + b.mem;
-    const int k = int(blockIdx.y) * int(blockDim.x) + int(threadIdx.x);
+    const int k = block_site(slices);
     if (k >= ch.count) return;
     const long long s = ch.start + k;
     double d, j[3];
@@ -379,11 +411,14 @@ hipError_t launch_init(int lat, int dtype, int K, int layout, const double* rho,
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
         constexpr int KK = decltype(Kc)::value;
-        const dim3 grid(unsigned(nchunks), unsigned((chunk_sites + 255) / 256));
+        const unsigned slices = unsigned((chunk_sites + 255) / 256);
+        const dim3 grid = chunk_grid(nchunks, slices);
         if (layout == kTwistEven)
-            k_init<L, S, KK, kTwistEven><<<grid, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites);
+            k_init<L, S, KK, kTwistEven><<<grid, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites,
+                                                              nchunks, slices);
         else
-            k_init<L, S, KK, kNatural><<<grid, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites);
+            k_init<L, S, KK, kNatural><<<grid, 256, 0, s>>>(rho, u, static_cast<S*>(dst), chunks, boxes, nsites,
+                                                            nchunks, slices);
         return hipGetLastError();
     });
 }
@@ -392,13 +427,15 @@ hipError_t launch_moments(int lat, int dtype, const void* src, int layout, doubl
                           const ChunkDesc* chunks, int nchunks, int chunk_sites, const BoxDesc* boxes,
                           long long nsites, hipStream_t s)
 {
-    const dim3 grid(unsigned(nchunks), unsigned((chunk_sites + 255) / 256));
+    const unsigned slices = unsigned((chunk_sites + 255) / 256);
+    const dim3 grid = chunk_grid(nchunks, slices);
     return dispatch_ld(lat, dtype, [&](auto Lt, auto* Sp, auto) -> hipError_t {
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
         return by_layout(layout, [&](auto Lay) -> hipError_t {
             constexpr int LAY = decltype(Lay)::value;
-            k_moments<L, S, LAY><<<grid, 256, 0, s>>>(static_cast<const S*>(src), rho, u, chunks, boxes, nsites);
+            k_moments<L, S, LAY><<<grid, 256, 0, s>>>(static_cast<const S*>(src), rho, u, chunks, boxes, nsites,
+                                                      nchunks, slices);
             return hipGetLastError();
         });
     });

@@ -302,3 +302,19 @@ def test_box_of_more_than_2_31_sites(kernel):
     # the reductions over 2^31 + 2^20 sites: ny copies of the slab's totals
     assert abs(tot[0] / (ny * tot1[0]) - 1) < 1e-12
     assert np.all(np.abs(tot[1:] - ny * tot1[1:]) <= 1e-12 * tot[0])
+
+
+@pytest.mark.parametrize("nbox,dims", [(32768, (3, 2, 2)), (32769, (3, 2, 2)), (70001, (2, 2, 1)), (40000, (7, 6, 8))])
+def test_more_boxes_than_a_row_of_the_set_up_grid(nbox, dims):
+    """Moments of the fields set in batches of many small boxes (the set-up and
+    moments grids hold 32768 chunks a row, one or two blocks each): FP64
+    equilibria of 19 terms of order one give back rho and u to a few units in
+    the last place of 1."""
+    from paper_2002_02503_amd import lbm
+
+    rng = np.random.default_rng(nbox)
+    n = nbox * int(np.prod(dims))
+    rho, u = 1.0 + rng.uniform(-0.01, 0.01, size=n), rng.uniform(-0.05, 0.05, size=(3, n))
+    with lbm.Simulation("D3Q19", [dims] * nbox, [0.7] * nbox, dtype="fp64") as sim:
+        r, v = sim.init(rho, u).moments()
+    assert np.abs(r - rho).max() <= 19 * 2.0**-52 and np.abs(v - u).max() <= 19 * 2.0**-52
