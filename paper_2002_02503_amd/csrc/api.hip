@@ -73,6 +73,10 @@ constexpr int kTuneRounds = 3;
 constexpr size_t kCachedStoresFrom = size_t(40) << 20;
 constexpr size_t kCachedStoresTo = size_t(128) << 20;
 
+// Largest state that the readers touch with the default cache policy: the
+// Infinity Cache holds much of it after a step.
+constexpr size_t kCachedReads = size_t(256) << 20;
+
 // Runs of the batched two-step kernel (step2_batch.hpp).
 constexpr int kRunPlanes = 16;
 constexpr int kMaxRounds = 12;
@@ -724,6 +728,18 @@ bool capturing(lbm_ctx* h)
     return true;
 }
 
+// How the readers touch the state and their fields.  Past the caches both are
+// touched once, but rows that do not start on a cache line share lines, which
+// non-temporal loads fetch twice.  D3Q19 FP32, us a call within a run of steps, all
+// cached / fields streamed / all streamed: residual of 256^3 312 / 287 / 282, of 200^3
+// (rows of 800 bytes) 163 / 150 / 171; totals 229 / - / 205 and 118 / - / 133; of 128^3,
+// whose state the cache holds, 37 / - / 41.
+int read_policy(const lbm_ctx* h)
+{
+    if (h->state_bytes <= kCachedReads) return kReadCached;
+    return (is_single(h) && size_t(h->dims[0]) * h->elem % 128 != 0) ? kStreamFields : kStreamAll;
+}
+
 // Where the current state is, and in which layout (StateLayout).
 void state_view(const lbm_ctx* h, const void** state, int* layout)
 {
@@ -1327,8 +1343,8 @@ lbm_status lbm_moments(lbm_t h, double* rho, double* u, int32_t on_device)
         const void* state = nullptr;
         int layout = kNatural;
         state_view(h, &state, &layout);
-        hipError_t e = launch_moments(h->lattice, h->dtype, state, layout, drho, du, h->d_chunks, h->nchunks,
-                                      h->chunk_sites, h->d_boxes, h->nsites, h->stream);
+        hipError_t e = launch_moments(h->lattice, h->dtype, state, layout, read_policy(h), drho, du, h->d_chunks,
+                                      h->nchunks, h->chunk_sites, h->d_boxes, h->nsites, h->stream);
         if (e == hipSuccess && !on_device) {
             e = hipMemcpyAsync(rho, drho, n * sizeof(double), hipMemcpyDeviceToHost, h->stream);
             if (e == hipSuccess) e = hipMemcpyAsync(u, du, n * D * sizeof(double), hipMemcpyDeviceToHost, h->stream);
@@ -1355,7 +1371,7 @@ lbm_status lbm_totals(lbm_t h, double* out)
         const void* state = nullptr;
         int layout = kNatural;
         state_view(h, &state, &layout);
-        hipError_t e = launch_totals(h->lattice, h->dtype, state, layout, h->d_chunks, h->nchunks,
+        hipError_t e = launch_totals(h->lattice, h->dtype, state, layout, read_policy(h), h->d_chunks, h->nchunks,
                                      h->d_box_chunk_begin, h->nbox, h->d_boxes, h->d_partial, h->d_out, h->stream);
         if (e != hipSuccess) return fail_hip(e, "totals kernels");
         HIP_TRY(hipMemcpyAsync(out, h->d_out, size_t(h->nbox) * 4 * sizeof(double), hipMemcpyDeviceToHost, h->stream),
@@ -1392,8 +1408,8 @@ lbm_status lbm_residual(lbm_t h, const double* rho_ref, const double* u_ref, int
         const void* state = nullptr;
         int layout = kNatural;
         state_view(h, &state, &layout);
-        hipError_t e = launch_residual(h->lattice, h->dtype, state, layout, dr, du, h->d_chunks, h->nchunks,
-                                       h->d_boxes, h->nsites, h->d_partial, h->d_out, false, h->stream);
+        hipError_t e = launch_residual(h->lattice, h->dtype, state, layout, read_policy(h), dr, du, h->d_chunks,
+                                       h->nchunks, h->d_boxes, h->nsites, h->d_partial, h->d_out, false, h->stream);
         double tmp[4] = {0, 0, 0, 0};
         if (e == hipSuccess) e = hipMemcpyAsync(tmp, h->d_out, 4 * sizeof(double), hipMemcpyDeviceToHost, h->stream);
         hipError_t e2 = hipStreamSynchronize(h->stream);
@@ -1433,8 +1449,8 @@ lbm_status lbm_residual_noalloc(lbm_t h, const double* rho_ref, const double* u_
         state_view(h, &state, &layout);
         // every partial slot the final kernel reads is written first by this
         // call, so nothing needs clearing
-        hipError_t e = launch_residual(h->lattice, h->dtype, state, layout, rho_ref, u_ref, h->d_chunks, h->nchunks,
-                                       h->d_boxes, h->nsites, partial, out, true, h->stream);
+        hipError_t e = launch_residual(h->lattice, h->dtype, state, layout, read_policy(h), rho_ref, u_ref,
+                                       h->d_chunks, h->nchunks, h->d_boxes, h->nsites, partial, out, true, h->stream);
         if (e != hipSuccess) return fail_hip(e, "residual kernels");
         return LBM_OK;
     } catch (...) {

@@ -123,6 +123,10 @@ struct ChunkDesc {
     int x0, y0, z0;
 };
 
+// What the readers of the state touch non-temporally: nothing; the fields that
+// they read or write beside it; those and the state.
+enum ReadPolicy { kReadCached, kStreamFields, kStreamAll };
+
 // Kernel launchers (kernels.hip).  All return hipSuccess or the first error.
 // chunk_sites: the largest chunk's sites.
 // layout: kNatural, or kTwistEven for a single box stepped by k_step_tw.
@@ -169,17 +173,17 @@ hipError_t launch_step2_batch(int lat, int dtype, int K, int kind, const void* s
                               const ColumnDesc* columns, const ColumnStart* starts, int rounds, double theta,
                               int grid, hipStream_t s);
 // Readers of the stored state, in any StateLayout (the in-place layouts for
-// a single box only).
-hipError_t launch_moments(int lat, int dtype, const void* src, int layout, double* rho, double* u,
+// a single box only).  read: a ReadPolicy.
+hipError_t launch_moments(int lat, int dtype, const void* src, int layout, int read, double* rho, double* u,
                           const ChunkDesc* chunks, int nchunks, int chunk_sites, const BoxDesc* boxes,
                           long long nsites, hipStream_t s);
-hipError_t launch_totals(int lat, int dtype, const void* src, int layout, const ChunkDesc* chunks, int nchunks,
+hipError_t launch_totals(int lat, int dtype, const void* src, int layout, int read, const ChunkDesc* chunks, int nchunks,
                          const int* box_chunk_begin, int nbox, const BoxDesc* boxes, double* partial, double* out,
                          hipStream_t s);
 // Error residuals: partial holds 4 doubles per chunk; out gets {max |du|,
 // sum du^2, max |drho|, sum drho^2}, or the square roots of the two sums when
 // sqrt_l2.
-hipError_t launch_residual(int lat, int dtype, const void* src, int layout, const double* rho_ref,
+hipError_t launch_residual(int lat, int dtype, const void* src, int layout, int read, const double* rho_ref,
                            const double* u_ref, const ChunkDesc* chunks, int nchunks, const BoxDesc* boxes,
                            long long nsites, double* partial, double* out, bool sqrt_l2, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);

@@ -159,8 +159,7 @@ __global__ __launch_bounds__(256) void k_init(const double* __restrict__ rho, co
 // rho - 1 and rho u (eq. mme) of one stored site, in double (outside the
 // step, for output and reductions).  `p` points at population 0 of the site,
 // w is the block width of the box's layout.
-// The state is read once: non-temporal loads.
-template <class L, class S>
+template <class L, class S, int READ>
 __device__ __forceinline__ void site_moments(const S* __restrict__ p, int w, double& dsum, double (&j)[3])
 {
     using ST = Store<S>;
@@ -170,7 +169,8 @@ __device__ __forceinline__ void site_moments(const S* __restrict__ p, int w, dou
         constexpr int i = decltype(I)::value;
         constexpr int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
         constexpr int m = mem_row<L>(i);
-        const double gi = double(ST::get_nt(p + (long long)m * w));
+        const S* q = p + (long long)m * w;
+        const double gi = double(READ == kStreamAll ? ST::get_nt(q) : ST::get(q));
         dsum += gi;
         if constexpr (cx != 0) j[0] += double(cx) * gi;
         if constexpr (cy != 0) j[1] += double(cy) * gi;
@@ -208,22 +208,20 @@ __device__ __forceinline__ void relaid_site_moments(const S* __restrict__ base, 
     if constexpr (L::D == 3) j[2] = over<L::S>(j[2]);
 }
 
-template <class L, class S, int LAYOUT>
+template <class L, class S, int LAYOUT, int READ>
 __device__ __forceinline__ void stored_site_moments(const S* __restrict__ base, const ChunkDesc& ch, int k,
                                                     const BoxDesc& b, double& dsum, double (&j)[3])
 {
     const SitePos pos = locate<LAYOUT != kNatural>(ch, k, b);
     if constexpr (LAYOUT != kNatural) relaid_site_moments<L, S, LAYOUT>(base, pos, b, dsum, j);
-    else site_moments<L, S>(base + site_elem<L::Q>(pos, b.w), b.w, dsum, j);
+    else site_moments<L, S, READ>(base + site_elem<L::Q>(pos, b.w), b.w, dsum, j);
 }
 
-// Bound by HBM.  From the natural layout the state is read and the fields are
-// written non-temporally: D3Q19 256^3, us a call, FP32 / FP16 / FP64: 315 / 211 /
-// 563, with cached loads 338 / 220 / 585, with cached stores 346 / 223 / 584, with
-// both cached 361 / 243 / 609.  The in-place layouts, whose cells are shared
-// between sites, keep the default policy (FP32 twisted 359-370, non-temporal
-// stores 375).
-template <class L, class S, int LAYOUT>
+// Bound by HBM.  D3Q19 256^3 from the natural layout, us a call within a run of
+// steps, FP32 / FP16 / FP64: 290 / 188 / 490 with the state and the fields touched
+// non-temporally, 331 / 216 / 577 with the default policy.  The in-place layouts,
+// whose cells are shared between sites, keep the default policy.
+template <class L, class S, int LAYOUT, int READ>
 __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ src, double* __restrict__ rho,
                                                  double* __restrict__ u, const ChunkDesc* __restrict__ chunks,
                                                  const BoxDesc* __restrict__ boxes, long long nsites, int nchunks,
@@ -238,10 +236,10 @@ __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ src, doub
     if (k >= ch.count) return;
     const long long s = ch.start + k;
     double d, j[3];
-    stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
+    stored_site_moments<L, S, LAYOUT, READ>(base, ch, k, b, d, j);
     const double r = 1.0 + d;
     auto put = [](double* q, double v) {
-        if constexpr (LAYOUT == kNatural) __builtin_nontemporal_store(v, q);
+        if constexpr (READ != kReadCached) __builtin_nontemporal_store(v, q);
         else *q = v;
     };
     put(rho + s, r);
@@ -252,8 +250,7 @@ __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ src, doub
 // ---------------------------------------------------------------------------
 // FP64 reductions with a fixed order: per-chunk partials (one block per
 // chunk, LDS tree), then per-box (or global) sums over chunks in order.  Bound
-// by HBM: non-temporal loads took the totals of D3Q19 256^3 FP32 from 243 to
-// 215 us and the residual from 327 to 294.
+// by HBM (api.hip, read_policy, on the loads).
 // ---------------------------------------------------------------------------
 
 constexpr int kRedBlock = 256;
@@ -278,7 +275,7 @@ __device__ __forceinline__ void block_tree(double (&acc)[NV], const bool (&is_ma
     for (int k = 0; k < NV; ++k) acc[k] = sh[k][0];
 }
 
-template <class L, class S, int LAYOUT>
+template <class L, class S, int LAYOUT, int READ>
 __global__ __launch_bounds__(kRedBlock) void k_totals_partial(const S* __restrict__ src,
                                                               const ChunkDesc* __restrict__ chunks,
                                                               const BoxDesc* __restrict__ boxes,
@@ -290,7 +287,7 @@ __global__ __launch_bounds__(kRedBlock) void k_totals_partial(const S* __restric
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int k = threadIdx.x; k < ch.count; k += kRedBlock) {
         double d, j[3];
-        stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
+        stored_site_moments<L, S, LAYOUT, READ>(base, ch, k, b, d, j);
         acc[0] += d;
         acc[1] += j[0];
         acc[2] += j[1];
@@ -323,7 +320,7 @@ __global__ __launch_bounds__(kRedBlock) void k_totals_final(const double* __rest
         for (int k = 0; k < 4; ++k) out[b * 4 + k] = acc[k];
 }
 
-template <class L, class S, int LAYOUT>
+template <class L, class S, int LAYOUT, int READ>
 __global__ __launch_bounds__(kRedBlock) void k_residual_partial(const S* __restrict__ src,
                                                                 const double* __restrict__ rho_ref,
                                                                 const double* __restrict__ u_ref,
@@ -334,19 +331,20 @@ __global__ __launch_bounds__(kRedBlock) void k_residual_partial(const S* __restr
     const ChunkDesc ch = chunks[blockIdx.x];
     const BoxDesc b = boxes[ch.box];
     const S* base = src + b.mem;
+    auto ref = [](const double* q) { return READ != kReadCached ? __builtin_nontemporal_load(q) : *q; };
     double acc[4] = {0.0, 0.0, 0.0, 0.0};  // max |du|, sum du^2, max |drho|, sum drho^2
     for (int k = threadIdx.x; k < ch.count; k += kRedBlock) {
         const long long s = ch.start + k;
         double d, j[3];
-        stored_site_moments<L, S, LAYOUT>(base, ch, k, b, d, j);
+        stored_site_moments<L, S, LAYOUT, READ>(base, ch, k, b, d, j);
         const double r = 1.0 + d;
 #pragma unroll
         for (int a = 0; a < L::D; ++a) {
-            const double du = j[a] / r - __builtin_nontemporal_load(u_ref + a * nsites + s);
+            const double du = j[a] / r - ref(u_ref + a * nsites + s);
             acc[0] = fmax(acc[0], fabs(du));
             acc[1] += du * du;
         }
-        const double dr = r - __builtin_nontemporal_load(rho_ref + s);
+        const double dr = r - ref(rho_ref + s);
         acc[2] = fmax(acc[2], fabs(dr));
         acc[3] += dr * dr;
     }
@@ -389,15 +387,20 @@ __global__ __launch_bounds__(256) void k_copy(const u32x4* __restrict__ src, u32
     if (k < n) __builtin_nontemporal_store(__builtin_nontemporal_load(src + k), dst + k);
 }
 
-// Calls f(integral_constant layout) for a runtime StateLayout.
+// Calls f(integral_constant layout, integral_constant policy) for a runtime
+// StateLayout and ReadPolicy; the in-place layouts, whose cells are shared
+// between sites, keep the default policy.
 template <class F>
-static hipError_t by_layout(int layout, F&& f)
+static hipError_t by_layout(int layout, int read, F&& f)
 {
     switch (layout) {
-    case kNatural: return f(ic<kNatural>{});
-    case kSwapped: return f(ic<kSwapped>{});
-    case kTwistEven: return f(ic<kTwistEven>{});
-    case kTwistOdd: return f(ic<kTwistOdd>{});
+    case kNatural:
+        return read == kStreamAll      ? f(ic<kNatural>{}, ic<kStreamAll>{})
+               : read == kStreamFields ? f(ic<kNatural>{}, ic<kStreamFields>{})
+                                       : f(ic<kNatural>{}, ic<kReadCached>{});
+    case kSwapped: return f(ic<kSwapped>{}, ic<kReadCached>{});
+    case kTwistEven: return f(ic<kTwistEven>{}, ic<kReadCached>{});
+    case kTwistOdd: return f(ic<kTwistOdd>{}, ic<kReadCached>{});
     default: return hipErrorInvalidValue;
     }
 }
@@ -423,7 +426,7 @@ hipError_t launch_init(int lat, int dtype, int K, int layout, const double* rho,
     });
 }
 
-hipError_t launch_moments(int lat, int dtype, const void* src, int layout, double* rho, double* u,
+hipError_t launch_moments(int lat, int dtype, const void* src, int layout, int read, double* rho, double* u,
                           const ChunkDesc* chunks, int nchunks, int chunk_sites, const BoxDesc* boxes,
                           long long nsites, hipStream_t s)
 {
@@ -432,25 +435,27 @@ hipError_t launch_moments(int lat, int dtype, const void* src, int layout, doubl
     return dispatch_ld(lat, dtype, [&](auto Lt, auto* Sp, auto) -> hipError_t {
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
-        return by_layout(layout, [&](auto Lay) -> hipError_t {
+        return by_layout(layout, read, [&](auto Lay, auto Read) -> hipError_t {
             constexpr int LAY = decltype(Lay)::value;
-            k_moments<L, S, LAY><<<grid, 256, 0, s>>>(static_cast<const S*>(src), rho, u, chunks, boxes, nsites,
+            constexpr int READ = decltype(Read)::value;
+            k_moments<L, S, LAY, READ><<<grid, 256, 0, s>>>(static_cast<const S*>(src), rho, u, chunks, boxes, nsites,
                                                       nchunks, slices);
             return hipGetLastError();
         });
     });
 }
 
-hipError_t launch_totals(int lat, int dtype, const void* src, int layout, const ChunkDesc* chunks, int nchunks,
+hipError_t launch_totals(int lat, int dtype, const void* src, int layout, int read, const ChunkDesc* chunks, int nchunks,
                          const int* box_chunk_begin, int nbox, const BoxDesc* boxes, double* partial, double* out,
                          hipStream_t s)
 {
     return dispatch_ld(lat, dtype, [&](auto Lt, auto* Sp, auto) -> hipError_t {
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
-        hipError_t e = by_layout(layout, [&](auto Lay) -> hipError_t {
+        hipError_t e = by_layout(layout, read, [&](auto Lay, auto Read) -> hipError_t {
             constexpr int LAY = decltype(Lay)::value;
-            k_totals_partial<L, S, LAY><<<nchunks, kRedBlock, 0, s>>>(static_cast<const S*>(src), chunks, boxes,
+            constexpr int READ = decltype(Read)::value;
+            k_totals_partial<L, S, LAY, READ><<<nchunks, kRedBlock, 0, s>>>(static_cast<const S*>(src), chunks, boxes,
                                                                       partial);
             return hipGetLastError();
         });
@@ -460,16 +465,17 @@ hipError_t launch_totals(int lat, int dtype, const void* src, int layout, const 
     });
 }
 
-hipError_t launch_residual(int lat, int dtype, const void* src, int layout, const double* rho_ref,
+hipError_t launch_residual(int lat, int dtype, const void* src, int layout, int read, const double* rho_ref,
                            const double* u_ref, const ChunkDesc* chunks, int nchunks, const BoxDesc* boxes,
                            long long nsites, double* partial, double* out, bool sqrt_l2, hipStream_t s)
 {
     return dispatch_ld(lat, dtype, [&](auto Lt, auto* Sp, auto) -> hipError_t {
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
-        hipError_t e = by_layout(layout, [&](auto Lay) -> hipError_t {
+        hipError_t e = by_layout(layout, read, [&](auto Lay, auto Read) -> hipError_t {
             constexpr int LAY = decltype(Lay)::value;
-            k_residual_partial<L, S, LAY><<<nchunks, kRedBlock, 0, s>>>(static_cast<const S*>(src), rho_ref, u_ref,
+            constexpr int READ = decltype(Read)::value;
+            k_residual_partial<L, S, LAY, READ><<<nchunks, kRedBlock, 0, s>>>(static_cast<const S*>(src), rho_ref, u_ref,
                                                                         chunks, boxes, nsites, partial);
             return hipGetLastError();
         });
@@ -525,7 +531,7 @@ hipError_t launch_relayout(int lat, int dtype, int layout, bool to_natural, cons
     return dispatch_ld(lat, dtype, [&](auto Lt, auto* Sp, auto) -> hipError_t {
         using L = decltype(Lt);
         using S = std::remove_pointer_t<decltype(Sp)>;
-        return by_layout(layout, [&](auto Lay) -> hipError_t {
+        return by_layout(layout, kReadCached, [&](auto Lay, auto) -> hipError_t {
             constexpr int LAY = decltype(Lay)::value;
             if constexpr (LAY != kNatural) {
                 if (to_natural)
