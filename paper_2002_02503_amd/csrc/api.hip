@@ -56,10 +56,11 @@ lbm_status fail_hip(hipError_t e, const char* what)
 constexpr int kChunkSites = 4096;   // most sites of a reduction chunk
 constexpr int kMinChunkSites = 256; // fewest, but for a box's last chunk
 // Small boxes take smaller chunks, down to one site per thread: a 16^3 box as
-// one chunk left a single block with sixteen loads in series (k_moments 19 us,
-// k_init 25 us).  2048 chunks are eight blocks per compute unit, where the
-// kernels are bound by HBM and larger chunks keep the final reduction short.
-constexpr int kManyChunks = 2048;
+// one chunk left a single block of the reductions with sixteen loads in series.
+// 1024 chunks are four blocks per compute unit, enough for the HBM rate; with
+// 2048 the lines that a block's next pass goes on with did not stay in its L2
+// (totals of D3Q19 FP64 140^3 72 us against 62, D3Q39 FP32 140^3 87 against 74).
+constexpr int kManyChunks = 1024;
 constexpr int kDefaultGraphChunk = 32;
 constexpr int kTuneRounds = 3;
 
