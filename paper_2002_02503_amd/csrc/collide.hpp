@@ -191,9 +191,9 @@ __device__ __forceinline__ void conserve(R (&G)[L::Q], R sd, R jx, R jy, R jz)
 //     Xe = E0 + c.M.c,           M = t / (2 T0^2) + n,
 //     Xo = c.l + a (c.N.c),      N = t / (6 T0^2) + n   (K = 3),
 //     E0 = (rho - 1) - tr t / (2 T0) - T0 tr n,   l = (1 + E0) u / T0 - 2 n.u,
-// (K = 2: Xo = rho a), and the rest particle has Xe = E0.  With n = 0 this is
-// the equilibrium that BGK relaxes to.  The energy flux adds Q.ccc - 3 T0 c.q
-// to Xo.
+// (K = 2: Xo = rho a, with a from u), and the rest particle has Xe = E0.  With
+// n = 0 this is the equilibrium that BGK relaxes to.  The energy flux adds
+// Q.ccc - 3 T0 c.q to Xo.
 // The conservation projection takes its sums from Xe and Xo (a pair's are 2 W Xe
 // and 2 W c Xo) and adds both corrections, dm +- c.dj / T0, to Xe before the
 // two populations are formed: Xe is the smaller of the two at low speed, so

@@ -58,8 +58,8 @@ constexpr int two_step_threads(size_t elem)
 
 // Threads of a block of the batched two-step kernel (step2_batch.hpp).  FP64:
 // what its two LDS planes leave room for (448 threads: 756 against 720 us per
-// step of 256 boxes of sides 16-64, 4 rounds).  Else 704: 1024 would fit too,
-// but ran at 360 us against 351 (8 rounds).
+// step of 256 boxes of sides 16-64, 17.6 million sites, 4 rounds).  Else 704:
+// 1024 would fit too, but ran at 360 us against 351 (8 rounds).
 constexpr int batch_columns_threads(size_t elem) { return elem == 8 ? 512 : 704; }
 
 // Whether the two-step kernel applies to a single nx x ny x nz box: a 3-D
@@ -79,8 +79,8 @@ bool columns_fit(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
 // piece, and as many rows as the block's threads hold.  A piece leaves room for
 // two rows at least (110 sites at most in FP64, where 111 to 128 left one):
 // step 1 takes three sites for each site of a single row, two for two.
-// Measured, us per step (tile): D3Q19 FP32 201 x 150 x 77 54 (101 x 4), 62 (67 x 8), 71 (51 x 11);
-// 100^3 21 (100 x 4), 29 (50 x 10), 33 (34 x 17); 255^3 363 (128 x 3), 411 (64 x
+// Measured, us per step (tile): D3Q19 FP32 201 x 150 x 77 54 (101 x 4), 62 (67 x
+// 8), 71 (51 x 11); 100^3 21 (100 x 4), 29 (50 x 10), 33 (34 x 17); 255^3 363 (128 x 3), 411 (64 x
 // 8); 160^3 83 (80 x 6 and 160 x 2), 93 (32 x 18); FP64 100^3 38 (100 x 2), 44
 // (50 x 6), 120^3 69 (60 x 5), 84 (120 x 1), 240^3 589 (80 x 3), 912 (120 x 1;
 // one-site step 706), 255^3 542 (85 x 3), 689 (128 x 1).  FP64 rows of whole lines
@@ -112,8 +112,8 @@ void batch_column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 // more sites (BF16 101^3 26 / 24, 130^3 43 / 50, FP16 201 x 150 x 77 41 / 48) and D3Q15
 // does not gain (BF16 130^3 39 / 35); nor do large states with rows of whole 32-byte
 // sectors that fill four fifths of the one-site step's lanes (BF16 160^3 74 / 64,
-// 240^3 285 / 244, but 208 x 120 x 120 50 / 54 and 400 x 200 x 100 163 / 180).  A box of one layer or of few rows computes
-// the ring for nothing: 1024 x 1024 x 1 37 / 28, 1000 x 1 x 1000 36 / 32, 100000 x 2 x 2
+// 240^3 285 / 244, but 208 x 120 x 120 50 / 54 and 400 x 200 x 100 163 / 180).  A box
+// of one layer or of few rows computes the ring for nothing: 1024 x 1024 x 1 37 / 28, 1000 x 1 x 1000 36 / 32, 100000 x 2 x 2
 // 18 / 13, but 512 x 512 x 2 13.9 / 15.6 and 1000 x 2 x 500 24 / 32.
 // Few planes: a column adds two planes of step 1, and a cut between blocks two
 // more.  Other tiles than the whole 64-column ones gain from three planes on in
@@ -141,9 +141,10 @@ bool columns_pay(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int64_
 // Whether the default for a batch is the two-step kernel: FP32 and FP64 batches
 // large enough in all and box by box, whose planes fill the blocks and whose
 // columns are not all ring.  D3Q19, us per step, one-step against two-step: 256
-// boxes of sides 16-64 FP32 437 / 347 and FP64 778 / 581, 24-40 215 / 181, 16-32 93 /
-// 89, 8-24 31 / 43; 16 boxes of 16-64 (820,000 sites) 24 / 20; 16-bit storage is
-// bound by instruction issue (256 boxes of 32-64 BF16 369 / 496).
+// boxes of sides 16-64 FP32 437 / 347 (17.2 million sites) and FP64 778 / 581
+// (15.4), 24-40 FP32 215 / 181, 16-32 93 / 89, 8-24 31 / 43; 16 boxes of 16-64
+// (820,000 sites) 24 / 20; 16-bit storage is bound by instruction issue (256
+// boxes of 32-64 BF16 369 / 496).
 // The shapes go by the rounds that the columns take over two steps, ring and the
 // two extra step-1 planes of a column included, against the two rounds of 256
 // sites: up to 1.8 times as many in FP32, where a plane counts four rounds at
@@ -181,8 +182,8 @@ bool tile_plan_fits(const LatticeInfo& L, int dtype, int64_t nx, int64_t ny, int
 //   - D2Q9: every size, but in 16-bit storage, whose steps are bound by
 //     instruction issue, only up to kTileShare16 sites per compute unit, and
 //     with more tiles than units not for a single row (100000 sites: 2.9 us per
-//     step one-site, 3.6 tiled; two rows of them 5.9 and 4.9).  Measured, us per step, one-site against the plan (tile,
-//     steps): 64^2 FP64 2.52 / 0.96 (8 x 4, 8), 256^2 FP32 3.29 / 1.65 (32 x 8,
+//     step one-site, 3.6 tiled; two rows of them 5.9 and 4.9).  Measured, us per
+//     step, one-site against the plan (tile, steps): 64^2 FP64 2.52 / 0.96 (8 x 4, 8), 256^2 FP32 3.29 / 1.65 (32 x 8,
 //     8), 601 x 400 FP32 5.9 / 3.2 (32 x 16, 5), 1024^2 FP32 14.4 / 8.0 and
 //     FP64 26.5 / 10.4 (32 x 16, 5), 4096^2 FP32 190 / 121; BF16 1024^2 9.1 / 9.9.
 //   - D3Q15 and D3Q19: up to kTileShare3d sites per compute unit.  The ring

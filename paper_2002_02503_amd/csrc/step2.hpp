@@ -78,7 +78,8 @@ __device__ __forceinline__ void walk_column(S (&lplane)[2][L::Q][NT], int za, in
     // Q moves a plane and Q registers but leaves only step 2 to hide the
     // latency.  Measured on D3Q19 256^3, us per step, early against late: FP64
     // 490 / 474, FP16 220 / 209, FP32 248 / 260, BF16 222 / 231, energy flux 287 /
-    // 286; the batched kernel (256 boxes of sides 16-64, FP32) 447 / 411.
+    // 286; the batched kernel (256 boxes of sides 16-64, 17.6 million sites, FP32)
+    // 447 / 411.
     constexpr bool LATE_LOADS = BATCH || std::is_same<S, double>::value || std::is_same<S, _Float16>::value;
     // held LDS values: read from the first plane on, used from the third
     // (k >= 2); zeroed so that no read is of an indeterminate value

@@ -15,9 +15,9 @@ namespace lbm {
 // from starts[k] up to starts[k + 1].  At any time the blocks then work on
 // neighbouring columns: the two rows that two columns of a box share meet in an
 // L2, and the reads spread over less memory.  Measured on 256 D3Q19 boxes of
-// sides 16-64, us per step with 1, 2, 4 and 8 rounds: FP32 415, 403, 368, 351
-// (one-step kernel 448), FP64 with 12 rounds 660 (1: 758; one-step 900).  Every
-// cut costs two more planes of step 1, so short runs are not cut further
+// sides 16-64 (17.6 million sites), us per step with 1, 2, 4 and 8 rounds: FP32
+// 415, 403, 368, 351 (one-step kernel 448), FP64 with 12 rounds 660 (1: 758;
+// one-step 900).  Every cut costs two more planes of step 1, so short runs are not cut further
 // (api.hip, build_columns).  Runs of z-chunks with the columns of a box side by
 // side in z were no faster (4 rounds: 380), nor were smaller tiles with two
 // blocks per compute unit (512 threads 438, 384 501).
