@@ -322,8 +322,8 @@ lbm_status build_tiles(lbm_ctx* h)
 }
 
 // Columns of the batched two-step kernel and the cuts that give every block an
-// equal share of them (step2_batch.hpp).  The cost of a column-plane is its
-// rounds in both steps; a column's two extra step-1 planes count with its first.
+// equal share of them (step2_batch.hpp).  A column-plane costs column_plane_cost
+// rounds; a column's two extra step-1 planes count with its first.
 lbm_status build_columns(lbm_ctx* h)
 {
     if (is_single(h) || h->d_starts) return LBM_OK;
@@ -341,7 +341,7 @@ lbm_status build_columns(lbm_ctx* h)
         c.box = b;
         c.mem = h->mem[b];
         c.omega = 1.0 - 1.0 / h->tau[b];
-        const int64_t r1 = column_rounds1(c.tx, c.ty), r = column_rounds(c.tx, c.ty);
+        const int64_t r1 = column_rounds1(c.tx, c.ty), r = column_plane_cost(c.tx, c.ty);
         for (c.y0 = 0; c.y0 < c.ny; c.y0 += c.ty)
             for (c.x0 = 0; c.x0 < c.nx; c.x0 += c.tx) {
                 columns.push_back(c);

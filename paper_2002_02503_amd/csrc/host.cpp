@@ -192,7 +192,7 @@ bool batch_columns_pay(const LatticeInfo& L, int dtype, int nbox, const int64_t*
         const int64_t nx = dims[3 * b], ny = dims[3 * b + 1], nz = dims[3 * b + 2];
         int tx = 0, ty = 0;
         batch_column_tile(size_t(elem), nx, ny, &tx, &ty);
-        const int64_t r = std::max(column_rounds(tx, ty), elem == 4 ? 4 : 0);
+        const int64_t r = elem == 4 ? column_plane_cost(tx, ty) : column_rounds(tx, ty);
         rounds += ((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * (nz * r + 2 * column_rounds1(tx, ty));
     }
     // 256 sites a round against two steps of every site

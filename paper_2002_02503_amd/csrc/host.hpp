@@ -94,6 +94,17 @@ void column_tile(size_t elem, int64_t nx, int64_t ny, int* tx, int* ty);
 constexpr int column_rounds1(int tx, int ty) { return ((tx + 2) * (ty + 2) + 255) / 256; }
 constexpr int column_rounds(int tx, int ty) { return column_rounds1(tx, ty) + (tx * ty + 255) / 256; }
 
+// What a plane costs a block of the batched two-step kernel, in rounds: four at
+// least, since the latency of a plane's loads and collisions shows when its
+// lanes are fewer.  With the bare rounds the blocks that got the small boxes of a
+// mixed batch ended last, after one-site steps were done (us per step, one-site,
+// bare rounds and these: 47 D3Q19 FP32 boxes of sides 12-56 47, 55 and 44, 159
+// D3Q15 of 11-39 47, 59 and 45; in FP64 the latter 93, 85 and 70).
+constexpr int column_plane_cost(int tx, int ty)
+{
+    return column_rounds(tx, ty) < 4 ? 4 : column_rounds(tx, ty);
+}
+
 // Column tile of the batched two-step kernel: x in even pieces of at most 128
 // (126 in FP64, for two rows: 30 boxes of 128 x 128 x 8 173 us per step, 227 with
 // one), and the rows that take the fewest rounds over the box, since the busiest
